@@ -1,26 +1,33 @@
-// Projection GEMMs of the prefill path on bf16 matrix cores (gfx950).
+// GEMMs of the prefill and the backward on bf16 matrix cores (gfx950).
 //
 // C[M][N] = A[M][K] * W[N][K]^T with both operands K-contiguous ([out, in]
-// weights), fp32 accumulation in v_mfma_f32_32x32x16_bf16, and two fused
-// epilogues:
-//   * QKV: Q of every layer and K, V of producers (Sec. 2.2, Eq. 1); RoPE is
-//     applied to Q and K in registers (the rotate-half partner of column c
-//     sits in the same lane, 64 columns on), then Q goes to its buffer, K to
-//     the producer's cache slot and V, transposed, to the V slot.  A consumer
-//     runs the same kernel with N = a * d_h (Q only).
-//   * residual: X_{l+1} = X_l + O W_O^T, with the residual stream read and
-//     written in fp32 between layers and a bf16 copy for the next projection.
+// weights), fp32 accumulation in v_mfma_f32_32x32x16_bf16, K summed in order in steps of
+// 16 whatever the tile (every tile size gives the same bits), and fused epilogues
+// (gemm_epi.h): RoPE + Q / K / V^T writes (Sec. 2.2, Eq. 1; a consumer runs it with
+// N = a * d_h, Q only), the residual update X_{l+1} = X_l + O W_O^T, or a plain store.
 //
-// Tiling: 256 x 256 x 64 per workgroup of 4 waves (2 x 2, 128 x 128 each, a
-// 4 x 4 grid of 32 x 32 MFMA blocks = 256 fp32 accumulators per lane).
-// Operand tiles go straight from global memory into LDS (global_load_lds_dwordx4,
-// no staging registers), double buffered (2 x 64 KB), one barrier per K step;
-// LDS rows are 128 B with the 16-byte chunk index XOR-swizzled by
-// ((row >> 1) & 7), which spreads the 32-row fragment reads over all 64 banks.  Tiles are ordered so that each XCD works on a contiguous group of
-// M-panels (its own L2 keeps the A and W panels hot).
+// gemm_big: 256 x 256 x 64 per workgroup of 8 waves, two per SIMD (waves w and w + 4), which
+// take turns: in every slot one group of four waves runs 16 matrix instructions from
+// registers while the other reads its next fragments from LDS and requests later tiles; a
+// barrier ends the slot and the groups change places.  One wave per SIMD (four waves of
+// 128 x 128) had nothing to run while it waited for its fragments and for the tile behind
+// the barrier.  Operands go from global memory straight into LDS, two stages of 64 KB; each
+// part of a stage is requested again as soon as its fragments are in registers, so a load
+// has two slots pairs (a whole K step of the workgroup) before its wait, which leaves the
+// newer loads in flight.
+//
+// gemm_small: BM x BN (128 x 128, 64 x 64) per workgroup of 4 waves, several workgroups per
+// CU, a ring of LDS stages: products whose 256 x 256 tiles would leave CUs without work.
+//
+// LDS rows are 128 B (64 k) with the 16-byte chunk index XOR-swizzled by ((row >> 1) & 7),
+// which spreads the fragment reads over all 64 banks.  Tiles are ordered so that each XCD
+// works on a contiguous group of M-panels (its own L2 keeps the A and W panels hot).
 #include "common.h"
+#include "gemm_epi.h"
 #include "kernels.h"
 #include "lds_tr.h"
+
+#include <algorithm>
 
 namespace kvp {
 namespace {
@@ -30,326 +37,6 @@ constexpr int BM = 256, BN = 256, BK = 64, NT = 256, GROUP_M = 8;
 // Word 3 of a raw buffer resource: a valid (32-bit) data format.
 constexpr int kRsrcWord3 = 0x00020000;
 
-__device__ __forceinline__ const uint16_t* w_row(const WRows& w, int n, int K) {
-    if (n < w.rows[0]) return (const uint16_t*)w.p[0] + (size_t)n * K;
-    n -= w.rows[0];
-    if (n < w.rows[1]) return (const uint16_t*)w.p[1] + (size_t)n * K;
-    n -= w.rows[1];
-    return (const uint16_t*)w.p[2] + (size_t)n * K;
-}
-
-// ---------------------------------------------------------------------------
-// Epilogues.  After the main loop each wave owns a 128 x 128 fp32 tile in
-// registers (lane: column n = 32 nb + l32, rows m = 32 mb + 8 (i/4) + 4 hi + i%4).
-// stage() writes it into the wave's 32 KB of the (now idle) LDS and flush()
-// copies it out with 16-byte coalesced global accesses, in Epi::kPasses passes.
-// ---------------------------------------------------------------------------
-
-// fp32 staging rows (128 x 64 fp32 = 256-byte rows, 16-byte chunk c): lanes write 128
-// contiguous bytes of rows m and m + 4, and read one chunk of 4 rows per 16 lanes; this
-// XOR keeps both patterns free of bank conflicts on the 64-bank LDS.
-__device__ __forceinline__ int f32_pos(int m, int c) {
-    return c ^ ((m & 1) | ((((m >> 1) ^ (m >> 2)) & 1) << 3));
-}
-__device__ __forceinline__ void st_f32(char* st, int m, int n, float v) {
-    *(float*)(st + m * 256 + f32_pos(m, n >> 2) * 16 + (n & 3) * 4) = v;
-}
-__device__ __forceinline__ u32x4 ld_f32(const char* st, int m, int c) {
-    return *(const u32x4*)(st + m * 256 + f32_pos(m, c) * 16);
-}
-
-// Q, K (rotated) and V (transposed) of the projection GEMM.  Q/K tiles go through LDS as
-// fp32 in two passes; pass h holds head columns 32 h .. 32 h + 31 and their rotate-half
-// partners 64 + 32 h .. 64 + 32 h + 31, so RoPE is applied in the flush with the cos/sin
-// of each (position, column) read as contiguous table rows.  V is staged once, in bf16,
-// transposed ([n][m], 8-byte unit u of row n at position u ^ (n & 31)).
-struct QkvEpi {
-    static constexpr int kPasses = 2;
-    // cos/sin rows of the lane's 8 Q/K items, requested before the tile is staged.
-    struct Pre {
-        u32x4 cs[8][4];
-    };
-    QkvOut o;
-    __device__ __forceinline__ void set_split(int) {}
-    // Element offsets of K row s and of V^T element (dimension n, position s) of
-    // sequence b, KV head `head`: in the contiguous slot or in s's page.
-    __device__ __forceinline__ size_t k_row(int b, int head, int s) const {
-        if (o.pages.pt)
-            return (((size_t)head * o.pages.n + page_at(o.pages, b, s / kPage)) * kPage + s % kPage) * 128;
-        return (((size_t)b * o.g + head) * o.cap + s) * 128;
-    }
-    __device__ __forceinline__ size_t v_at(int b, int head, int n, int s) const {
-        if (o.pages.pt)
-            return (((size_t)head * o.pages.n + page_at(o.pages, b, s / kPage)) * 128 + n) * kPage + s % kPage;
-        return (((size_t)b * o.g + head) * 128 + n) * o.cap + s;
-    }
-    // Region of the wave's 128 columns: 0 = Q, 1 = K, 2 = V, -1 = past N.
-    __device__ __forceinline__ int region(int nw, int N, int* head) const {
-        if (nw >= N) return -1;
-        if (nw < o.n_q) { *head = nw >> 7; return 0; }
-        if (nw < o.n_q + o.n_kv) { *head = (nw - o.n_q) >> 7; return 1; }
-        *head = (nw - o.n_q - o.n_kv) >> 7;
-        return 2;
-    }
-    __device__ __forceinline__ void stage(int pass, f32x16 (&acc)[4][4], int mw, int nw, int lane,
-                                          int M, int N, char* st) const {
-        int head;
-        const int reg = region(nw, N, &head);
-        if (reg < 0) return;
-        const int l32 = lane & 31, hi = lane >> 5;
-        if (reg == 2) {
-            if (pass != 0) return;
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4)
-#pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) {
-                        const int n = 32 * nb + l32, u = 8 * mb + 2 * r4 + hi;
-                        u32x2 v;
-                        v[0] = pack2bf(acc[mb][nb][4 * r4 + 0], acc[mb][nb][4 * r4 + 1]);
-                        v[1] = pack2bf(acc[mb][nb][4 * r4 + 2], acc[mb][nb][4 * r4 + 3]);
-                        *(u32x2*)(st + n * 256 + ((u ^ (n & 31)) * 8)) = v;
-                    }
-            return;
-        }
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 32 * mb + 8 * (i >> 2) + 4 * hi + (i & 3);
-                st_f32(st, m, l32, pass == 0 ? acc[mb][0][i] : acc[mb][1][i]);
-                st_f32(st, m, 32 + l32, pass == 0 ? acc[mb][2][i] : acc[mb][3][i]);
-            }
-    }
-    // Item t of the lane: staging row (lane + 64 t) / 4, rotation pairs 8 ((lane + 64 t) % 4) ..
-    // + 7 of the pass's 32.
-    __device__ __forceinline__ void prefetch(int pass, int mw, int nw, int lane, int M, int N,
-                                             Pre& pre) const {
-        int head;
-        const int reg = region(nw, N, &head);
-        if (reg != 0 && reg != 1) return;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int id = lane + 64 * t;
-            const int m = min(mw + (id >> 2), M - 1);
-            const int c0 = 32 * pass + 8 * (id & 3);
-            const u32x4* tab = (const u32x4*)(o.rope + (size_t)(m % o.S) * 64 + c0);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) pre.cs[t][q] = tab[q];
-        }
-    }
-    __device__ __forceinline__ void flush(int pass, int mw, int nw, int lane, int M, int N,
-                                          const char* st, const Pre& pre) const {
-        int head;
-        const int reg = region(nw, N, &head);
-        if (reg < 0) return;
-        if (reg == 2) {
-            if (pass != 0) return;
-            // V^T rows: 16 lanes x 16 bytes = one 128-position row n.
-            const bool fast = (o.S % 8) == 0;
-#pragma unroll 4
-            for (int it = 0; it < 32; ++it) {
-                const int n = 4 * it + (lane >> 4), k = lane & 15;   // chunk k = positions 8k..8k+7
-                const int m = mw + 8 * k;
-                if (m >= M) continue;
-                const int sw = n & 31;
-                const u32x2 lo = *(const u32x2*)(st + n * 256 + (((2 * k) ^ sw) * 8));
-                const u32x2 up = *(const u32x2*)(st + n * 256 + (((2 * k + 1) ^ sw) * 8));
-                const int b = m / o.S, s = m - b * o.S;
-                if (fast && m + 7 < M) {
-                    // s % 8 == 0: the 8 positions never straddle a 64-position page.
-                    *(u32x4*)(o.vc + v_at(b, head, n, s)) = u32x4{lo[0], lo[1], up[0], up[1]};
-                } else {
-                    const uint32_t w4[4] = {lo[0], lo[1], up[0], up[1]};
-                    for (int e = 0; e < 8 && m + e < M; ++e) {
-                        int bb = b, ss = s + e;
-                        while (ss >= o.S) { ss -= o.S; ++bb; }
-                        o.vc[v_at(bb, head, n, ss)] = (bf16_t)(w4[e >> 1] >> (16 * (e & 1)));
-                    }
-                }
-            }
-            return;
-        }
-        // Q / K: 128 rows x 4 groups of 8 rotation pairs; 8 items per lane (cos/sin rows from
-        // prefetch()).
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int id = lane + 64 * t, k = id & 3, rowl = id >> 2;
-            const int m = mw + rowl;
-            if (m >= M) continue;
-            const u32x4 a0 = ld_f32(st, rowl, 2 * k), a1 = ld_f32(st, rowl, 2 * k + 1);
-            const u32x4 b0 = ld_f32(st, rowl, 8 + 2 * k), b1 = ld_f32(st, rowl, 9 + 2 * k);
-            float x1[8], x2[8], c[8], sn[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                x1[e] = __uint_as_float(a0[e]);
-                x1[e + 4] = __uint_as_float(a1[e]);
-                x2[e] = __uint_as_float(b0[e]);
-                x2[e + 4] = __uint_as_float(b1[e]);
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                c[e] = __uint_as_float(pre.cs[t][e >> 1][2 * (e & 1)]);
-                sn[e] = __uint_as_float(pre.cs[t][e >> 1][2 * (e & 1) + 1]);
-            }
-            u32x4 lo, up;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                lo[e] = pack2bf(x1[2 * e] * c[2 * e] - x2[2 * e] * sn[2 * e],
-                                x1[2 * e + 1] * c[2 * e + 1] - x2[2 * e + 1] * sn[2 * e + 1]);
-                up[e] = pack2bf(x2[2 * e] * c[2 * e] + x1[2 * e] * sn[2 * e],
-                                x2[2 * e + 1] * c[2 * e + 1] + x1[2 * e + 1] * sn[2 * e + 1]);
-            }
-            const int c0 = 32 * pass + 8 * k;
-            uint16_t* dst;
-            if (reg == 0) {
-                dst = o.q + (size_t)m * o.n_q + head * 128;
-            } else {
-                const int b = m / o.S;
-                dst = o.kc + k_row(b, head, m - b * o.S);
-            }
-            *(u32x4*)(dst + c0) = lo;
-            *(u32x4*)(dst + c0 + 64) = up;
-        }
-    }
-};
-
-// Residual update y = x + acc.  x is the bf16 layer input (XF32 = false) or the fp32
-// residual stream (XF32 = true, updated in place through yf); y is written in bf16,
-// yf (optional) in fp32.  The fp32 tile is staged in two passes of 64 columns
-// (128 x 64 fp32 = 32 KB per wave in 256-byte rows).
-template <bool XF32>
-struct ResidEpi {
-    static constexpr int kPasses = 2;
-    // The lane's 16 residual items (row, 8 columns), requested before the tile is staged.
-    struct Pre {
-        u32x4 xv[16][XF32 ? 2 : 1];
-    };
-    const void* x;
-    uint16_t* y;
-    float* yf;
-    __device__ __forceinline__ void set_split(int) {}
-    __device__ __forceinline__ void stage(int pass, f32x16 (&acc)[4][4], int mw, int nw, int lane,
-                                          int M, int N, char* st) const {
-        if (nw >= N) return;
-        const int l32 = lane & 31, hi = lane >> 5;
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 32 * mb + 8 * (i >> 2) + 4 * hi + (i & 3);
-                st_f32(st, m, l32, pass == 0 ? acc[mb][0][i] : acc[mb][2][i]);
-                st_f32(st, m, 32 + l32, pass == 0 ? acc[mb][1][i] : acc[mb][3][i]);
-            }
-    }
-    // Item it of the lane: row 8 it + lane / 8, columns 8 (lane % 8) .. + 7 of the pass's 64.
-    __device__ __forceinline__ void prefetch(int pass, int mw, int nw, int lane, int M, int N,
-                                             Pre& pre) const {
-        if (nw >= N) return;
-#pragma unroll
-        for (int it = 0; it < 16; ++it) {
-            const int ml = 8 * it + (lane >> 3), c8 = lane & 7;
-            const size_t off = (size_t)min(mw + ml, M - 1) * N + nw + 64 * pass + 8 * c8;
-            if (XF32) {
-                pre.xv[it][0] = *(const u32x4*)((const float*)x + off);
-                pre.xv[it][XF32 ? 1 : 0] = *(const u32x4*)((const float*)x + off + 4);
-            } else {
-                pre.xv[it][0] = *(const u32x4*)((const uint16_t*)x + off);
-            }
-        }
-    }
-    __device__ __forceinline__ void flush(int pass, int mw, int nw, int lane, int M, int N,
-                                          const char* st, const Pre& pre) const {
-        if (nw >= N) return;
-        const auto& xv = pre.xv;
-#pragma unroll
-        for (int it = 0; it < 16; ++it) {
-            const int ml = 8 * it + (lane >> 3), c8 = lane & 7;
-            const int m = mw + ml;
-            if (m >= M) continue;
-            const u32x4 p0 = ld_f32(st, ml, 2 * c8), p1 = ld_f32(st, ml, 2 * c8 + 1);
-            float r[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float a0 = __uint_as_float(p0[e]), a1 = __uint_as_float(p1[e]);
-                float x0, x1;
-                if (XF32) {
-                    x0 = __uint_as_float(xv[it][0][e]);
-                    x1 = __uint_as_float(xv[it][XF32 ? 1 : 0][e]);
-                } else {
-                    const uint32_t w0 = xv[it][0][e >> 1], w1 = xv[it][0][2 + (e >> 1)];
-                    x0 = __uint_as_float((e & 1) ? (w0 & 0xFFFF0000u) : (w0 << 16));
-                    x1 = __uint_as_float((e & 1) ? (w1 & 0xFFFF0000u) : (w1 << 16));
-                }
-                r[e] = x0 + a0;
-                r[4 + e] = x1 + a1;
-            }
-            const size_t off = (size_t)m * N + nw + 64 * pass + 8 * c8;
-            u32x4 out;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) out[e] = pack2bf(r[2 * e], r[2 * e + 1]);
-            *(u32x4*)(y + off) = out;
-            if (yf) {
-                *(u32x4*)(yf + off) = u32x4{__float_as_uint(r[0]), __float_as_uint(r[1]),
-                                            __float_as_uint(r[2]), __float_as_uint(r[3])};
-                *(u32x4*)(yf + off + 4) = u32x4{__float_as_uint(r[4]), __float_as_uint(r[5]),
-                                                __float_as_uint(r[6]), __float_as_uint(r[7])};
-            }
-        }
-    }
-};
-
-// Plain store of C (no fused work): bf16 [M][N], or fp32 partial sums of one K slice into
-// plane `split` of out ([M][N] per plane).  Staged like ResidEpi, two passes of 64 columns.
-struct OutEpi {
-    static constexpr int kPasses = 2;
-    struct Pre {};
-    void* out;
-    size_t plane;
-    int split;
-    bool bf16;
-    __device__ __forceinline__ void set_split(int s) { split = s; }
-    __device__ __forceinline__ void stage(int pass, f32x16 (&acc)[4][4], int mw, int nw, int lane,
-                                          int M, int N, char* st) const {
-        if (nw >= N) return;
-        const int l32 = lane & 31, hi = lane >> 5;
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 32 * mb + 8 * (i >> 2) + 4 * hi + (i & 3);
-                st_f32(st, m, l32, pass == 0 ? acc[mb][0][i] : acc[mb][2][i]);
-                st_f32(st, m, 32 + l32, pass == 0 ? acc[mb][1][i] : acc[mb][3][i]);
-            }
-    }
-    __device__ __forceinline__ void prefetch(int, int, int, int, int, int, Pre&) const {}
-    __device__ __forceinline__ void flush(int pass, int mw, int nw, int lane, int M, int N,
-                                          const char* st, const Pre&) const {
-        if (nw >= N) return;
-#pragma unroll
-        for (int it = 0; it < 16; ++it) {
-            const int ml = 8 * it + (lane >> 3), c8 = lane & 7;
-            const int m = mw + ml;
-            if (m >= M) continue;
-            const u32x4 p0 = ld_f32(st, ml, 2 * c8), p1 = ld_f32(st, ml, 2 * c8 + 1);
-            const size_t off = (size_t)m * N + nw + 64 * pass + 8 * c8;
-            if (bf16) {
-                u32x4 o;
-                o[0] = pack2bf(__uint_as_float(p0[0]), __uint_as_float(p0[1]));
-                o[1] = pack2bf(__uint_as_float(p0[2]), __uint_as_float(p0[3]));
-                o[2] = pack2bf(__uint_as_float(p1[0]), __uint_as_float(p1[1]));
-                o[3] = pack2bf(__uint_as_float(p1[2]), __uint_as_float(p1[3]));
-                *(u32x4*)((uint16_t*)out + off) = o;
-            } else {
-                float* dst = (float*)out + split * plane + off;
-                *(u32x4*)dst = p0;
-                *(u32x4*)(dst + 4) = p1;
-            }
-        }
-    }
-};
-
 typedef __attribute__((address_space(1))) void gvoid_t;
 typedef __attribute__((address_space(3))) void lvoid_t;
 
@@ -357,180 +44,358 @@ typedef __attribute__((address_space(3))) void lvoid_t;
 // rows of one chunk column over all 64 banks.
 __device__ __forceinline__ int swz(int r, int c) { return c ^ ((r >> 1) & 7); }
 
-// BUF: operand tiles are fetched with buffer loads into LDS, each lane's 8 + 8 offsets
-// computed once and the k-tile advance given as the scalar offset, so issuing a tile costs
-// no vector instructions (operands below 2 GiB; a wave's 64 W rows lie in one weight block
-// since block sizes and N are multiples of 128).
-template <class Epi, bool BUF>
-__global__ __launch_bounds__(NT, 1) void gemm_bf16_nt(const uint16_t* __restrict__ A, WRows W,
-                                                     int M, int N, int K, int splits, Epi epi) {
-    __shared__ u32x4 lds[2][2][BM * 8];  // [stage][A, W][row * 8 + swizzled chunk]
+// Buffer resource of `rows` rows of K values at p: reads past them return zeros.  Made
+// scalar word by word (a resource in vector registers costs a loop around every load).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const uint16_t* p, int rows, int K) {
+    const uint64_t a = (uint64_t)p;
+    const uint64_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)a) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32;
+    return __builtin_amdgcn_make_buffer_rsrc((void*)u, 0, __builtin_amdgcn_readfirstlane(max(rows, 0) * K * 2),
+                                             kRsrcWord3);
+}
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+// First row of the 128-row weight block at stacked row n (n % 128 == 0, block sizes are
+// multiples of 128).
+__device__ __forceinline__ const uint16_t* w_block(const WRows& w, int n, int K) {
+    if (n < w.rows[0]) return (const uint16_t*)w.p[0] + (size_t)n * K;
+    n -= w.rows[0];
+    if (n < w.rows[1]) return (const uint16_t*)w.p[1] + (size_t)n * K;
+    n -= w.rows[1];
+    return (const uint16_t*)w.p[2] + (size_t)n * K;
+}
+
+// Tile of workgroup `lid` (row tile, column tile): groups of gm row tiles, rows fastest.
+__device__ __forceinline__ void tile_of(int lid, int ntm, int ntn, int gm, int& tm, int& tn) {
+    const int group = lid / (gm * ntn), first = group * gm;
+    const int gsz = min(ntm - first, gm);
+    const int in_g = lid - group * gm * ntn;
+    tm = first + in_g % gsz;
+    tn = in_g / gsz;
+}
+
+// Fragment reads: four 16-wide k steps of one or two 32-row blocks per operand, addresses
+// per k step plus a constant for the block.  The reads and their wait are one asm block: the
+// compiler, which cannot tell the LDS stages apart, would wait for every load into LDS
+// before a plain read.
+typedef u32x4 Frag[4];   // [k step]
+// A rows +0 and +32, B rows +0 and +128.
+__device__ __forceinline__ void read_a2b2_half(Frag (&fa)[2], Frag (&fb)[2], const uint32_t (&a)[4],
+                                            const uint32_t (&b)[4]) {
+    asm volatile("ds_read_b128 %0, %16\n\tds_read_b128 %4, %16 offset:4096\n\t"
+                 "ds_read_b128 %8, %20\n\tds_read_b128 %12, %20 offset:16384\n\t"
+                 "ds_read_b128 %1, %17\n\tds_read_b128 %5, %17 offset:4096\n\t"
+                 "ds_read_b128 %9, %21\n\tds_read_b128 %13, %21 offset:16384\n\t"
+                 "ds_read_b128 %2, %18\n\tds_read_b128 %6, %18 offset:4096\n\t"
+                 "ds_read_b128 %10, %22\n\tds_read_b128 %14, %22 offset:16384\n\t"
+                 "ds_read_b128 %3, %19\n\tds_read_b128 %7, %19 offset:4096\n\t"
+                 "ds_read_b128 %11, %23\n\tds_read_b128 %15, %23 offset:16384\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(fa[0][0]), "=&v"(fa[0][1]), "=&v"(fa[0][2]), "=&v"(fa[0][3]), "=&v"(fa[1][0]),
+                   "=&v"(fa[1][1]), "=&v"(fa[1][2]), "=&v"(fa[1][3]), "=&v"(fb[0][0]), "=&v"(fb[0][1]),
+                   "=&v"(fb[0][2]), "=&v"(fb[0][3]), "=&v"(fb[1][0]), "=&v"(fb[1][1]), "=&v"(fb[1][2]),
+                   "=&v"(fb[1][3])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3])
+                 : "memory");
+}
+// A and B rows +0 and +32.
+__device__ __forceinline__ void read_a2b2(Frag (&fa)[2], Frag (&fb)[2], const uint32_t (&a)[4],
+                                            const uint32_t (&b)[4]) {
+    asm volatile("ds_read_b128 %0, %16\n\tds_read_b128 %4, %16 offset:4096\n\t"
+                 "ds_read_b128 %8, %20\n\tds_read_b128 %12, %20 offset:4096\n\t"
+                 "ds_read_b128 %1, %17\n\tds_read_b128 %5, %17 offset:4096\n\t"
+                 "ds_read_b128 %9, %21\n\tds_read_b128 %13, %21 offset:4096\n\t"
+                 "ds_read_b128 %2, %18\n\tds_read_b128 %6, %18 offset:4096\n\t"
+                 "ds_read_b128 %10, %22\n\tds_read_b128 %14, %22 offset:4096\n\t"
+                 "ds_read_b128 %3, %19\n\tds_read_b128 %7, %19 offset:4096\n\t"
+                 "ds_read_b128 %11, %23\n\tds_read_b128 %15, %23 offset:4096\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(fa[0][0]), "=&v"(fa[0][1]), "=&v"(fa[0][2]), "=&v"(fa[0][3]), "=&v"(fa[1][0]),
+                   "=&v"(fa[1][1]), "=&v"(fa[1][2]), "=&v"(fa[1][3]), "=&v"(fb[0][0]), "=&v"(fb[0][1]),
+                   "=&v"(fb[0][2]), "=&v"(fb[0][3]), "=&v"(fb[1][0]), "=&v"(fb[1][1]), "=&v"(fb[1][2]),
+                   "=&v"(fb[1][3])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3])
+                 : "memory");
+}
+// A rows +128 and +160.
+__device__ __forceinline__ void read_a2_upper(Frag (&fa)[2], const uint32_t (&a)[4]) {
+    asm volatile("ds_read_b128 %0, %8 offset:16384\n\tds_read_b128 %4, %8 offset:20480\n\t"
+                 "ds_read_b128 %1, %9 offset:16384\n\tds_read_b128 %5, %9 offset:20480\n\t"
+                 "ds_read_b128 %2, %10 offset:16384\n\tds_read_b128 %6, %10 offset:20480\n\t"
+                 "ds_read_b128 %3, %11 offset:16384\n\tds_read_b128 %7, %11 offset:20480\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(fa[0][0]), "=&v"(fa[0][1]), "=&v"(fa[0][2]), "=&v"(fa[0][3]), "=&v"(fa[1][0]),
+                   "=&v"(fa[1][1]), "=&v"(fa[1][2]), "=&v"(fa[1][3])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+                 : "memory");
+}
+// One block of A and one of B.
+__device__ __forceinline__ void read_a1b1(Frag& fa, Frag& fb, const uint32_t (&a)[4], const uint32_t (&b)[4]) {
+    asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %4, %12\n\t"
+                 "ds_read_b128 %1, %9\n\tds_read_b128 %5, %13\n\t"
+                 "ds_read_b128 %2, %10\n\tds_read_b128 %6, %14\n\t"
+                 "ds_read_b128 %3, %11\n\tds_read_b128 %7, %15\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(fa[0]), "=&v"(fa[1]), "=&v"(fa[2]), "=&v"(fa[3]), "=&v"(fb[0]), "=&v"(fb[1]), "=&v"(fb[2]),
+                   "=&v"(fb[3])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3])
+                 : "memory");
+}
+
+// 64 lanes x 16 bytes at r + voff + soff (bytes) to 1 KB of LDS at dst.
+__device__ __forceinline__ void load_1k(__amdgpu_buffer_rsrc_t r, u32x4* dst, uint32_t voff, int soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lvoid_t*)dst, 16, voff, soff, 0, 0);
+}
+
+template <int N>
+__device__ __forceinline__ void vm_wait() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
+}
+__device__ __forceinline__ void slot_end() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+constexpr int kBigNT = 512;
+
+// Slots.  A K tile is two phases: phase a multiplies tile rows 0..127 (each wave 64 of them)
+// by all columns, phase b rows 128..255; a phase is a read slot and a product slot, and the
+// second wave group runs one slot behind the first.  Tile parts A0, A1 (rows 0..127,
+// 128..255) and B0, B1 (columns likewise) of tile kt + 2 are requested into stage kt % 2 once
+// both groups have read tile kt's (A0, B0, B1: in phase b of tile kt; A1: in phase a of tile
+// kt + 1), 16 KB each, two loads per wave.  Every read slot ends with a wait for the parts
+// the next phase reads; at most the 8 newer loads stay in flight.  MODE 1 and 2 are the last
+// two tiles: nothing (but A1) left to request, so the waits count down.
+template <class Epi>
+__global__ __launch_bounds__(kBigNT, 2) void gemm_big(const uint16_t* __restrict__ A, WRows W, int M, int N, int K,
+                                                     int splits, Epi epi) {
+    __shared__ u32x4 lds[8192];   // A [stage][half][128 rows][8 chunks], then B likewise
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const int l32 = lane & 31, hi = lane >> 5;
 
     const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
     // With split K, workgroup slot `split` of every tile takes K columns
     // [split * K / splits, (split + 1) * K / splits); consecutive ids share a slice.
     const int lid0 = xcd_remap(blockIdx.x, gridDim.x);
-    const int split = lid0 / (ntm * ntn);
-    const int lid = lid0 - split * (ntm * ntn);
-    const int kofs = split * (K / splits);
+    const int split = __builtin_amdgcn_readfirstlane(lid0 / (ntm * ntn));
+    int tm, tn;
+    tile_of(lid0 - split * (ntm * ntn), ntm, ntn, GROUP_M, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int kslice = __builtin_amdgcn_readfirstlane(K / splits);
+    const int kofs = split * kslice, nk = kslice / BK;
     epi.set_split(split);
-    const int group = lid / (GROUP_M * ntn), first = group * GROUP_M;
-    const int gsz = min(ntm - first, GROUP_M);
-    const int in_g = lid - group * GROUP_M * ntn;
-    const int m0 = (first + in_g % gsz) * BM, n0 = (in_g / gsz) * BN;
 
-    // Direct global -> LDS loads: wave w fills tile rows 64 w .. 64 w + 63 of A and of W,
-    // eight 1 KB instructions each (8 rows of 128 B); lane l of instruction j covers row
-    // 64 w + 8 j + l / 8 and fetches the global chunk that belongs at LDS position l % 8.
-    const uint16_t* a_src[8];
-    const uint16_t* w_src[8];
-    uint32_t ga_off[8], gw_off[8];
-    __amdgpu_buffer_rsrc_t ars, wrs;
-    if constexpr (BUF) {
-        const int wu = __builtin_amdgcn_readfirstlane(wave);
-        ars = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, M * K * 2, kRsrcWord3);
-        const int x = n0 + 64 * wu;              // tile row 64 w (past N if the wave has no real row)
-        int nb = min(x, N - 1), blk = 0;
-        if (nb >= W.rows[0]) {
-            nb -= W.rows[0];
-            blk = 1;
-            if (nb >= W.rows[1]) {
-                nb -= W.rows[1];
-                blk = 2;
-            }
-        }
-        const int rows_blk = W.rows[blk];
-        wrs = __builtin_amdgcn_make_buffer_rsrc((void*)W.p[blk], 0, rows_blk * K * 2, kRsrcWord3);
-        const int nrow0 = nb + (x - min(x, N - 1));   // block row of tile row 64 w (rows past the block clamp)
+    // Resources of the four half tiles; a half past M has no rows, one past N repeats the first.
+    const __amdgpu_buffer_rsrc_t ra[2] = {row_rsrc(A + (size_t)m0 * K, min(M - m0, 128), K),
+                                          row_rsrc(A + (size_t)(m0 + (m0 + 128 < M ? 128 : 0)) * K, min(M - m0 - 128, 128), K)};
+    const __amdgpu_buffer_rsrc_t rb[2] = {row_rsrc(w_block(W, n0, K), 128, K),
+                                          row_rsrc(w_block(W, n0 + 128 < N ? n0 + 128 : n0, K), 128, K)};
+    // Wave w requests rows 16 w .. 16 w + 15 of a half in two 1 KB instructions (8 rows each);
+    // lane l covers row l / 8 and fetches the global chunk that belongs at position l % 8.
+    uint32_t goff[2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int row = 64 * wave + 8 * j + (lane >> 3);
-            const int c = swz(row, lane & 7);
-            ga_off[j] = (uint32_t)(min(m0 + row, M - 1) * K + kofs + 8 * c) * 2u;
-            gw_off[j] = (uint32_t)(min(nrow0 + 8 * j + (lane >> 3), rows_blk - 1) * K + kofs + 8 * c) * 2u;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int row = 64 * wave + 8 * j + (lane >> 3);
-            const int c = swz(row, lane & 7);
-            a_src[j] = A + (size_t)min(m0 + row, M - 1) * K + kofs + 8 * c;
-            w_src[j] = w_row(W, min(n0 + row, N - 1), K) + kofs + 8 * c;
-        }
+    for (int j = 0; j < 2; ++j) {
+        const int row = 16 * wave + 8 * j + (lane >> 3);
+        goff[j] = (uint32_t)(row * K + kofs + 8 * swz(row, lane & 7)) * 2u;
     }
-    // Row group j (8 rows of A and of W) of tile kt into stage stg.
-    auto issue_part = [&](int kt, int stg, int j) {
-        const int r0 = 64 * (BUF ? __builtin_amdgcn_readfirstlane(wave) : wave) + 8 * j;
-        if constexpr (BUF) {
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ars, (lvoid_t*)&lds[stg][0][r0 * 8], 16, ga_off[j], kt * BK * 2,
-                                                     0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lvoid_t*)&lds[stg][1][r0 * 8], 16, gw_off[j], kt * BK * 2,
-                                                     0, 0);
-        } else {
-            __builtin_amdgcn_global_load_lds((gvoid_t*)(a_src[j] + kt * BK), (lvoid_t*)&lds[stg][0][r0 * 8], 16,
-                                             0, 0);
-            __builtin_amdgcn_global_load_lds((gvoid_t*)(w_src[j] + kt * BK), (lvoid_t*)&lds[stg][1][r0 * 8], 16,
-                                             0, 0);
-        }
-    };
-    auto issue = [&](int kt, int stg) {
+    // A tile past the last one is requested at offsets past the resource: nothing is fetched,
+    // and the wait counts stay the same to the end.
+    auto issue = [&](const __amdgpu_buffer_rsrc_t& r, int part, int half, int kt) __attribute__((always_inline)) {
+        u32x4* dst = &lds[part * 4096 + ((kt & 1) * 2 + half) * 1024 + wave * 128];
+        const uint32_t past = kt < nk ? 0u : 0x80000000u;
+        const int ko = kt < nk ? kt * BK * 2 : 0;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) issue_part(kt, stg, j);
+        for (int j = 0; j < 2; ++j)
+            load_1k(r, dst + 64 * j, goff[j] | past, ko);
     };
 
-    f32x16 acc[4][4];
+    // LDS byte addresses of the lane's fragments (k step ks) in half 0 of stage 0.
+    uint32_t aa[4], ab[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
-
-    const int nk = K / splits / BK;
-    const int l32 = lane & 31, hi = lane >> 5;
-    int a_off[4], b_off[4], rsw[4], bsw[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int ra = wm * 128 + 32 * i + l32, rb = wn * 128 + 32 * i + l32;
-        a_off[i] = ra * 8;
-        b_off[i] = rb * 8;
-        rsw[i] = (ra >> 1) & 7;
-        bsw[i] = (rb >> 1) & 7;
+    for (int ks = 0; ks < 4; ++ks) {
+        const uint32_t c = (uint32_t)(((2 * ks + hi) ^ ((l32 >> 1) & 7)) * 16);
+        aa[ks] = (uint32_t)(uintptr_t)&lds[(64 * wm + l32) * 8] + c;
+        ab[ks] = (uint32_t)(uintptr_t)&lds[4096 + (32 * wn + l32) * 8] + c;
     }
-    auto load_frags = [&](int stg, int ks, bf16x8 (&fa)[4], bf16x8 (&fb)[4]) {
-        const int c = 2 * ks + hi;
+    f32x16 acc[2][2][2];   // [row half][column half][32-row block]
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            fa[i] = as_bf16x8(lds[stg][0][a_off[i] + (c ^ rsw[i])]);
-            fb[i] = as_bf16x8(lds[stg][1][b_off[i] + (c ^ bsw[i])]);
-        }
+    for (int i = 0; i < 8; ++i) acc[i >> 2][(i >> 1) & 1][i & 1] = f32x16{};
+    Frag fa[2], fb[2];
+    // The products stay in their slot: nothing else orders them against the barriers.
+    auto products = [&](f32x16 (&c)[2][2]) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(c[0][0]), "+v"(c[0][1]), "+v"(c[1][0]), "+v"(c[1][1]));
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+                    c[j][mb] = mfma32x32x16(as_bf16x8(fa[mb][ks]), as_bf16x8(fb[j][ks]), c[j][mb]);
+        __builtin_amdgcn_s_setprio(0);
+        asm volatile("" : "+v"(c[0][0]), "+v"(c[0][1]), "+v"(c[1][0]), "+v"(c[1][1]));
     };
-
-    issue(0, 0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-
-    bf16x8 fa[4], fb[4], ga[4], gb[4];
-    load_frags(0, 0, fa, fb);
+    issue(ra[0], 0, 0, 0);
+    issue(rb[0], 1, 0, 0);
+    issue(rb[1], 1, 1, 0);
+    issue(ra[1], 0, 1, 0);
+    issue(ra[0], 0, 0, 1);
+    issue(rb[0], 1, 0, 1);
+    issue(rb[1], 1, 1, 1);
+    vm_wait<8>();
+    slot_end();
+    if (wm == 1) slot_end();   // the second group runs one slot behind
     for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < nk;
-        // Four 16-wide k steps; the fragments of step ks + 1 are read from LDS while the
-        // 16 MFMAs of step ks run (one ds_read slotted after each of the first 8 MFMAs).
-        // Tile kt + 1 goes into the other buffer (last read before the barrier that ended
-        // step kt - 1) in two halves, with the first two k steps: issued in one burst its
-        // LDS writes collide with the fragment reads; spread over all four steps the last
-        // loads land too close to the end-of-tile wait (measured: 4 % / 5 % faster GEMMs
-        // than the burst at K = 2048 / 8192).
+        // phase a
+        issue(ra[1], 0, 1, kt + 1);
+        read_a2b2_half(fa, fb, aa, ab);
+        vm_wait<8>();
+        slot_end();
+        products(acc[0]);
+        slot_end();
+        // phase b
+        issue(ra[0], 0, 0, kt + 2);
+        issue(rb[0], 1, 0, kt + 2);
+        issue(rb[1], 1, 1, kt + 2);
+        read_a2_upper(fa, aa);
+        vm_wait<8>();
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            if (more && ks < 2) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) issue_part(kt + 1, cur ^ 1, 4 * ks + j);
-            }
-            if (ks < 3) load_frags(cur, ks + 1, ga, gb);
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = mfma32x32x16(fa[mb], fb[nb], acc[mb][nb]);
-            if (ks < 3) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
-                }
-                __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    fa[i] = ga[i];
-                    fb[i] = gb[i];
-                }
-            }
+            aa[ks] ^= 32768u;
+            ab[ks] ^= 32768u;
         }
-        if (more) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of tile kt + 1
-            __syncthreads();                                    // everyone's part, and tile kt read
-            load_frags(cur ^ 1, 0, fa, fb);
-        }
+        slot_end();
+        products(acc[1]);
+        slot_end();
     }
-    // Epilogue through LDS, in Epi::kPasses passes over the wave's 32 KB.  The pass's global
-    // inputs (cos/sin rows, residual) are requested before the staging, so that their latency
-    // runs under the LDS writes and the barrier.
-    char* st = (char*)&lds[0][0][0] + wave * 32768;
+    if (wm == 0) slot_end();
+    vm_wait<0>();
+    // Pass i: rows 128 i .. + 127 of the tile.
+    char* st = (char*)&lds[0];
 #pragma unroll
-    for (int pass = 0; pass < Epi::kPasses; ++pass) {
+    for (int i = 0; i < 2; ++i) {
         __syncthreads();   // the LDS is free: last fragment reads / previous flush are done
-        typename Epi::Pre pre;
-        epi.prefetch(pass, m0 + wm * 128, n0 + wn * 128, lane, M, N, pre);
-        epi.stage(pass, acc, m0 + wm * 128, n0 + wn * 128, lane, M, N, st);
+        typename Epi::template Pre<128, BN, kBigNT> pre;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) st_block<BN>(st, acc[i][j][mb], 64 * wm + 32 * mb, 128 * j + 32 * wn, lane);
+        // Requested in the registers that the staging has freed.
+        __builtin_amdgcn_sched_barrier(0);
+        epi.template prefetch<128, BN, kBigNT>(m0 + 128 * i, n0, tid, M, N, pre);
         __syncthreads();
-        epi.flush(pass, m0 + wm * 128, n0 + wn * 128, lane, M, N, st, pre);
+        epi.template flush<128, BN, kBigNT>(m0 + 128 * i, n0, tid, M, N, st, pre);
     }
 }
 
+// BM_ x BN_ tile of 4 waves (2 x 2), STAGES K tiles in LDS: tile kt + STAGES - 1 is requested
+// once tile kt - 1 is read, and a wave waits only for tile kt's loads, so STAGES - 1 tiles of
+// latency are covered; other workgroups of the CU run under the rest.
+template <class Epi, int BM_, int BN_, int STAGES, int GM>
+__global__ __launch_bounds__(256, 2) void gemm_small(const uint16_t* __restrict__ A, WRows W, int M, int N, int K,
+                                                    int splits, Epi epi) {
+    constexpr int ROWS = BM_ + BN_, LPT = ROWS / 32;   // LDS rows of a stage, loads per wave and tile
+    constexpr int MB = BM_ / 64, NB = BN_ / 64;
+    static_assert((MB == 2 && NB == 2) || (MB == 1 && NB == 1), "fragment reads are written for these tiles");
+    __shared__ u32x4 lds[STAGES * ROWS * 8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l32 = lane & 31, hi = lane >> 5;
+
+    const int ntm = (M + BM_ - 1) / BM_, ntn = (N + BN_ - 1) / BN_;
+    const int lid0 = xcd_remap(blockIdx.x, gridDim.x);
+    const int split = __builtin_amdgcn_readfirstlane(lid0 / (ntm * ntn));
+    int tm, tn;
+    tile_of(lid0 - split * (ntm * ntn), ntm, ntn, GM, tm, tn);
+    const int m0 = tm * BM_, n0 = tn * BN_;
+    const int kslice = __builtin_amdgcn_readfirstlane(K / splits);
+    const int kofs = split * kslice, nk = kslice / BK;
+    epi.set_split(split);
+
+    const __amdgpu_buffer_rsrc_t ra = row_rsrc(A + (size_t)m0 * K, min(M - m0, BM_), K);
+    const __amdgpu_buffer_rsrc_t rb = row_rsrc(w_block(W, n0 & ~127, K), 128, K);
+    // LDS rows 8 u .. 8 u + 7 (u = wave * LPT + j): A's rows, then B's.
+    uint32_t goff[LPT];
+#pragma unroll
+    for (int j = 0; j < LPT; ++j) {
+        const int r = 8 * (wave * LPT + j) + (lane >> 3);
+        int row = r;
+        if (r >= BM_) {
+            row = r - BM_;
+            if (BN_ == 64) row = Epi::kPairedCols ? (n0 & 64) / 2 + (row & 31) + 2 * (row & 32) : (n0 & 64) + row;
+        }
+        goff[j] = (uint32_t)(row * K + kofs + 8 * swz(r, lane & 7)) * 2u;
+    }
+    auto issue = [&](int kt, int stg) __attribute__((always_inline)) {
+        u32x4* dst = &lds[(stg * ROWS + 8 * wave * LPT) * 8];
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+            if (8 * (wave * LPT + j) < BM_)
+                load_1k(ra, dst + 64 * j, goff[j], kt * BK * 2);
+            else
+                load_1k(rb, dst + 64 * j, goff[j], kt * BK * 2);
+        }
+    };
+    f32x16 acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x16{};
+
+    // Tiles past the last one are requested again as the last: the wait counts stay the same
+    // and their stages are never read.
+#pragma unroll
+    for (int t = 0; t < STAGES - 1; ++t) issue(min(t, nk - 1), t);
+    int stg = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        vm_wait<LPT * (STAGES - 2)>();
+        slot_end();   // tile kt has landed for every wave, and every wave has read tile kt - 1
+        issue(min(kt + STAGES - 1, nk - 1), stg == 0 ? STAGES - 1 : stg - 1);
+        uint32_t aa[4], ab[4];
+        const uint32_t base = (uint32_t)(uintptr_t)&lds[0] + stg * (ROWS * 128);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const uint32_t c = (uint32_t)(((2 * ks + hi) ^ ((l32 >> 1) & 7)) * 16);
+            aa[ks] = base + (wm * (BM_ / 2) + l32) * 128 + c;
+            ab[ks] = base + (BM_ + wn * (BN_ / 2) + l32) * 128 + c;
+        }
+        if constexpr (MB == 2) {
+            Frag fa[2], fb[2];
+            read_a2b2(fa, fb, aa, ab);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = mfma32x32x16(as_bf16x8(fa[i][ks]), as_bf16x8(fb[j][ks]), acc[i][j]);
+        } else {
+            Frag fa, fb;
+            read_a1b1(fa, fb, aa, ab);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) acc[0][0] = mfma32x32x16(as_bf16x8(fa[ks]), as_bf16x8(fb[ks]), acc[0][0]);
+        }
+        stg = stg + 1 == STAGES ? 0 : stg + 1;
+    }
+    vm_wait<0>();
+    __syncthreads();   // no load into LDS is in flight and every fragment is read
+    static_assert(BM_ * BN_ * 4 <= STAGES * ROWS * 128, "the tile is staged in one pass");
+    char* st = (char*)&lds[0];
+    typename Epi::template Pre<BM_, BN_, 256> pre;
+    epi.template prefetch<BM_, BN_, 256>(m0, n0, tid, M, N, pre);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) st_block<BN_>(st, acc[i][j], wm * (BM_ / 2) + 32 * i, wn * (BN_ / 2) + 32 * j, lane);
+    __syncthreads();
+    epi.template flush<BM_, BN_, 256>(m0, n0, tid, M, N, st, pre);
+}
+
 // ---------------------------------------------------------------------------
-// The same tiling for C[M][N] = sum_k A[k][m] B[k][n] with both operands given K-major
+// 256 x 256 x 64 tiles of 4 waves (128 x 128 each) for C[M][N] = sum_k A[k][m] B[k][n] with both operands given K-major
 // ([K][rows], rows contiguous): the weight gradients dW_O = G^T O and
 // dW_QKV = [dQ|dK|dV]^T X of the backward, whose K is the token axis.  Each operand tile is
 // staged as [64 k][256 rows] in the sub-tiled layout and its MFMA fragments are taken along
@@ -660,30 +525,54 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_g(Operand<TA> Aop, Operand<TB
             }
         }
     }
-    char* st = (char*)&lds[0][0][0] + wave * 32768;
+    char* st = (char*)&lds[0][0][0];
 #pragma unroll
-    for (int pass = 0; pass < Epi::kPasses; ++pass) {
+    for (int pass = 0; pass < 2; ++pass) {   // rows 128 pass .. + 127: the waves with wm == pass
         __syncthreads();
-        typename Epi::Pre pre;
-        epi.prefetch(pass, m0 + wm * 128, n0 + wn * 128, lane, M, N, pre);
-        epi.stage(pass, acc, m0 + wm * 128, n0 + wn * 128, lane, M, N, st);
+        typename Epi::template Pre<128, BN, NT> pre;
+        epi.template prefetch<128, BN, NT>(m0 + 128 * pass, n0, tid, M, N, pre);
+        if (wm == pass)
+#pragma unroll
+            for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                for (int nb2 = 0; nb2 < 4; ++nb2) st_block<BN>(st, acc[mb][nb2], 32 * mb, wn * 128 + 32 * nb2, lane);
         __syncthreads();
-        epi.flush(pass, m0 + wm * 128, n0 + wn * 128, lane, M, N, st, pre);
+        epi.template flush<128, BN, NT>(m0 + 128 * pass, n0, tid, M, N, st, pre);
     }
+}
+
+// Estimated time (us) of a product on each tile, k = K / 1024, t = number of tiles: fitted to
+// the layer projections at widths 2048, 4096 and 8192 and 64 to 16384 tokens.  A 256 x 256
+// tile has a CU to itself; a round costs 13 + 13.5 k with few CUs busy and 17.5 + 21.7 k with
+// all of them (the matrix cores' clock falls, the epilogues share the HBM).  The small tiles
+// run two workgroups per CU: a floor for one wave of workgroups, then 512 at a time.
+// Measured (us, 256 / 128 / 64): 200 tokens at width 4096, Q|K|V 73 / 44 / 26; 1024 tokens
+// at 2048, output 40 / 25 / 18; 3000 tokens at 2048, Q|K|V 55 / 59 / 81, output 42 / 33 / 43;
+// 8192 tokens at 8192, Q|K|V 978 / 1217 / 2407.
+int pick_tile(int M, int N, int K, int splits) {
+    const float k = (float)K / (float)splits / 1024.f;
+    auto tiles = [&](int b) { return (int64_t)((M + b - 1) / b) * ((N + b - 1) / b) * splits; };
+    const int64_t t = tiles(256), rest = t % 256;
+    float big = (float)(t / 256) * (17.5f + 21.7f * k);
+    if (rest) big += 13.f + 13.5f * k + (float)rest / 256.f * (4.5f + 8.2f * k);
+    const float mid = std::max(7.f + 8.8f * k, (float)tiles(128) / 512.f * (9.f + 13.4f * k));
+    const float low = std::max(6.5f + 3.5f * k, (float)tiles(64) / 512.f * (8.f + 5.1f * k));
+    if (low < mid && low < big) return 64;
+    return mid < big ? 128 : 256;
 }
 
 template <class Epi>
 hipError_t launch(const uint16_t* A, const WRows& W, int M, int N, int K, const Epi& epi,
                   hipStream_t st, int splits = 1) {
-    const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    bool buf = (int64_t)M * K * 2 < ((int64_t)1 << 31) && N % 128 == 0;
-    for (int i = 0; i < 3; ++i) buf = buf && (int64_t)W.rows[i] * K * 2 < ((int64_t)1 << 31) && W.rows[i] % 128 == 0;
-    if (buf)
-        hipLaunchKernelGGL((gemm_bf16_nt<Epi, true>), dim3(tiles * splits), dim3(NT), 0, st, A, W, M, N, K, splits,
-                           epi);
+    if (M < 1 || N % 128 || splits < 1 || K % (BK * splits)) return hipErrorInvalidValue;
+    const int b = pick_tile(M, N, K, splits);
+    const dim3 grid(((M + b - 1) / b) * ((N + b - 1) / b) * splits);
+    if (b == 64)
+        hipLaunchKernelGGL((gemm_small<Epi, 64, 64, 4, 16>), grid, dim3(256), 0, st, A, W, M, N, K, splits, epi);
+    else if (b == 128)
+        hipLaunchKernelGGL((gemm_small<Epi, 128, 128, 2, 8>), grid, dim3(256), 0, st, A, W, M, N, K, splits, epi);
     else
-        hipLaunchKernelGGL((gemm_bf16_nt<Epi, false>), dim3(tiles * splits), dim3(NT), 0, st, A, W, M, N, K,
-                           splits, epi);
+        hipLaunchKernelGGL(gemm_big<Epi>, grid, dim3(kBigNT), 0, st, A, W, M, N, K, splits, epi);
     return hipGetLastError();
 }
 

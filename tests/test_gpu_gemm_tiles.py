@@ -1,0 +1,67 @@
+"""The projection GEMMs choose a tile size from the product's sizes.  Layer forwards at sizes
+that take each tile, with row and column remainders of it (rows that fill no tile, an odd
+number of heads so that the last column tile is half empty), against the fp64 oracle at the
+bf16 tolerance; and, since every tile sums K in the same order, the same sequence alone and
+inside a large batch gives the same bits."""
+import numpy as np
+import pytest
+import torch
+
+import kvp_inputs as ki
+from kvp_inputs import device as kd
+from oracle import attention as oat
+from paper_2608_15943_amd import binding as kb
+
+from gpu_util import DEV, build_device_model, oracle_weights, rel_err, say, small_workload, to_np, tol, workspace
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    kb.lib()
+
+
+def _forward(dm, B, S):
+    w = dm.w
+    x = torch.empty((B, S, w.h), dtype=torch.bfloat16, device=DEV)
+    kd.fill_prefill_x(w, x.data_ptr(), B, S)
+    y, o = torch.empty_like(x), torch.empty_like(x)
+    ws, n = workspace(dm, kb.KVP_PHASE_PREFILL, B, S)
+    dm.model.kvp_layer_forward(0, x.data_ptr(), o.data_ptr(), y.data_ptr(), B, S, ws.data_ptr(), n,
+                               torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return y, o
+
+
+@pytest.mark.parametrize("a,g,B,S", [
+    (1, 1, 1, 1),        # one row, 64-wide tiles
+    (3, 1, 1, 63),
+    (3, 1, 1, 65),
+    (3, 3, 3, 43),       # 129 rows, positions not a multiple of 8
+    (3, 1, 40, 67),
+    (3, 1, 300, 67),     # 20100 rows: 128-wide tiles, 4 rows in the last
+    (16, 8, 33, 127),    # 4191 rows at width 2048: 256-wide tiles, 95 rows in the last
+    (33, 3, 245, 67),    # 16415 rows at width 4224: 256-wide tiles, the last column tile half empty
+])
+def test_layer_forward_over_the_tile_sizes(a, g, B, S):
+    w = small_workload(f"tiles-a{a}-g{g}", 1, a * 128, a, g, [0])
+    say(f"[gemm tiles] h={w.h} g={g} B={B} S={S}")
+    cap = (S + 63) // 64 * 64
+    dm = build_device_model(w, B, S, cap)
+    y, o = _forward(dm, B, S)
+    K, V = dm.slots[0]
+    K, V = K.clone(), V.clone()
+    ow = oracle_weights(w)
+    for b in sorted({0, B - 1}):
+        ref, _, _, caches = oat.stack_prefill(ki.prefill_x(w, [b], np.arange(S))[0], ow, w.tau, w.a, w.g, w.d_h,
+                                              w.rope_base)
+        assert rel_err(to_np(y[b]), ref) <= tol(w), b
+        assert rel_err(to_np(K[b, :, :S]), caches[0][0]) <= tol(w), b
+        assert rel_err(to_np(V[b, :, :, :S]).transpose(0, 2, 1), caches[0][1]) <= tol(w), b
+    assert torch.isfinite(y.float()).all() and torch.isfinite(o.float()).all()
+    y1, o1 = _forward(dm, 1, S)
+    assert torch.equal(y1[0], y[0]) and torch.equal(o1[0], o[0])
+    assert torch.equal(dm.slots[0][0][0], K[0]) and torch.equal(dm.slots[0][1][0], V[0])
