@@ -1,186 +1,375 @@
-// Backward of the KV-shared layer for fp32 models (the small configurations): plain fp32
-// on the vector ALUs, the same data flow as the bf16 path.  With S = Q K^T / sqrt(d)
-// (masked), P = softmax(S), O = P V (Sec. 2.2, Eq. 2): dV = P^T dO, dP = dO V^T,
-// dS = P * (dP - D), D = rowsum(dO * O), dQ = dS K / sqrt(d), dK = dS^T Q / sqrt(d); dQ and
-// dK are rotated back through RoPE (orthogonal per position); a consumer's dK, dV add into
-// its producer's fp32 sums (Eq. 3).  One thread per output row; d <= 128.
+// Attention of fp32 models over whole sequences (the small configurations), forward and
+// backward: plain fp32 on the vector ALUs, the same data flow as the bf16 path.  With
+// S = Q K^T / sqrt(d) (masked), P = softmax(S), O = P V (Sec. 2.2, Eq. 2): dV = P^T dO,
+// dP = dO V^T, dS = P * (dP - D), D = rowsum(dO * O), dQ = dS K / sqrt(d),
+// dK = dS^T Q / sqrt(d); dQ and dK are rotated back through RoPE (orthogonal per position); a
+// consumer's dK, dV add into its producer's fp32 sums (Eq. 3).
+//
+// A workgroup owns 16 queries of one head (forward, dQ) or 16 keys of one KV head (dK, dV);
+// its four waves take every fourth tile of the other axis (attn_f32.h).  Measured on the
+// four-layer stack (128 tokens, 4 heads of 64), per layer, against one thread per row with
+// rows read from global memory: dK/dV 1150 -> 19 us, dQ and the row statistics 719 -> 21 us;
+// the forward 22 -> 14 us against one wave per (token, head).  Unrolling the row loops or
+// masking by selects instead of branches made all three slower (14 -> 17, 21 -> 26, 19 -> 27
+// us): a kernel this short also pays for the instructions it fetches.
+//
+// A key or query outside the causal mask is never multiplied into a sum, so a value that is
+// not finite reaches only the rows that see it.
 #include <math.h>
 
-#include "common.h"
+#include "attn_f32.h"
 #include "kernels.h"
 
 namespace kvp {
 namespace {
 
-// C[m][n] = R[m][n] + sum_k A(m, k) B(k, n) (R = 0 when res is null; res may equal c) with
-// A(m, k) = a[m * sam + k * sak], B(k, n) = b[k * sbk + n * sbn]; C and R row stride ldc.
-// One wave per (row, 64 columns): A is read wave-uniformly, B and C along rows.
-__global__ __launch_bounds__(256) void gemm_f32s_kernel(const float* __restrict__ a, size_t sam, size_t sak,
-                                                        const float* __restrict__ b, size_t sbk, size_t sbn,
-                                                        const float* res, float* c, size_t ldc, int M, int N,
-                                                        int K) {
-    const int n = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int m = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (m >= M || n >= N) return;
-    float s = 0.f;
-    for (int k = 0; k < K; ++k) s = fmaf(a[m * sam + k * sak], b[k * sbk + n * sbn], s);
-    const size_t o = (size_t)m * ldc + n;
-    c[o] = res ? res[o] + s : s;
+// Running softmax of the lane's row over a tile's scaled scores (-inf where hidden): returns
+// the factor of what was summed before.
+__device__ __forceinline__ float softmax_step(float (&s)[4], float& m, float& l) {
+    const float mt = quad_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+    const float mn = fmaxf(m, mt);
+    // A row that has seen no key yet (rows past the end) keeps its empty sum.
+    const float a = mn == -INFINITY ? 1.f : expf(m - mn);
+    float t = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        s[e] = mn == -INFINITY ? 0.f : expf(s[e] - mn);
+        t += s[e];
+    }
+    l = l * a + quad_sum(t);
+    m = mn;
+    return a;
 }
 
-// Per (token, head): the log-sum-exp of the scaled causal scores and D = dO . O.
 template <int D>
-__global__ __launch_bounds__(64) void stats_f32_kernel(const float* __restrict__ q, const float* __restrict__ kc,
-                                                       const float* __restrict__ dO, const float* __restrict__ O,
-                                                       float* __restrict__ lse, float* __restrict__ dsum, int B,
-                                                       int S, int a, int g, int cap) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * S * a) return;
-    const int r = idx / a, h = idx - r * a, kvh = h / (a / g);
-    const int b = r / S, pos = r - b * S;
+__global__ __launch_bounds__(256) void attn_tile_f32_kernel(const float* __restrict__ q, const float* __restrict__ kc,
+                                                            const float* __restrict__ vc, float* __restrict__ o, int B,
+                                                            int S, int a, int g, int cap) {
+    constexpr int P = F32Tile<D>::P, N4 = D / 16;
+    __shared__ F32Tile<D> qs, ks[4], vs[4];
+    __shared__ float ps[4][FT][FT + 1], ml[4][2][FT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane >> 2, c = lane & 3;
+    const int nqt = (S + FT - 1) / FT;
+    const int qt = nqt - 1 - blockIdx.x / (B * a), bh = blockIdx.x % (B * a);   // longest rows first
+    const int b = bh / a, h = bh - b * a, kvh = h / (a / g);
+    const int q0 = qt * FT;
     const float scale = 1.0f / sqrtf((float)D);
-    const float* qr = q + ((size_t)r * a + h) * D;
     const float* kb = kc + ((size_t)b * g + kvh) * cap * D;
+    const float* vb = vc + ((size_t)b * g + kvh) * D * cap;
+    {
+        RowLoad<D, 256> x;
+        x.load(q + ((size_t)(b * S + q0) * a + h) * D, (size_t)a * D, min(S - q0, FT), tid);
+        x.store(qs, tid);
+    }
+    __syncthreads();
+    f32x4 acc[N4];
+#pragma unroll
+    for (int i = 0; i < N4; ++i) acc[i] = f32x4{};
     float m = -INFINITY, l = 0.f;
-    for (int t = 0; t <= pos; ++t) {
-        float s = 0.f;
-        for (int i = 0; i < D; ++i) s = fmaf(qr[i], kb[(size_t)t * D + i], s);
-        s *= scale;
-        const float m_new = fmaxf(m, s);
-        l = l * expf(m - m_new) + expf(s - m_new);
-        m = m_new;
+    RowLoad<D, 64> kl;
+    ColLoad<D, 64> vl;
+    auto fetch = [&](int t) {
+        kl.load(kb + (size_t)t * FT * D, D, min(S - t * FT, FT), lane);
+        vl.load(vb + t * FT, cap, min(S - t * FT, FT), lane);
+    };
+    if (wave <= qt) fetch(wave);
+    for (int t = wave; t <= qt; t += 4) {
+        wave_sync();
+        kl.store(ks[wave], lane);
+        vl.store(vs[wave], lane);
+        if (t + 4 <= qt) fetch(t + 4);
+        wave_sync();
+        float s[4];
+        dot_tile<D>(qs, ks[wave], r, c, s);
+        const int lim = min(q0 + r, S - 1) - t * FT;      // last visible key of the row in the tile
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = 4 * c + e <= lim ? s[e] * scale : -INFINITY;
+        const float f = softmax_step(s, m, l);
+#pragma unroll
+        for (int i = 0; i < N4; ++i) acc[i] *= f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ps[wave][r][4 * c + e] = s[e];
+        wave_sync();
+        for (int j = 0; j < FT; ++j)
+            if (j <= lim) add_row<D>(acc, vs[wave], j, c, ps[wave][r][j]);
     }
-    lse[idx] = m + logf(l);
-    float dd = 0.f;
-    for (int i = 0; i < D; ++i) dd = fmaf(dO[((size_t)r * a + h) * D + i], O[((size_t)r * a + h) * D + i], dd);
-    dsum[idx] = dd;
+    // Merge the waves: weights exp(m_w - M), in wave order.
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < N4; ++i) *(f32x4*)&ks[wave].v[r * P + 16 * i + 4 * c] = acc[i];
+    if (c == 0) {
+        ml[wave][0][r] = m;
+        ml[wave][1][r] = l;
+    }
+    __syncthreads();
+    for (int id = tid; id < FT * D; id += 256) {
+        const int row = id / D, d = id % D;
+        if (q0 + row >= S) continue;
+        const float M = fmaxf(fmaxf(ml[0][0][row], ml[1][0][row]), fmaxf(ml[2][0][row], ml[3][0][row]));
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float wt = expf(ml[w][0][row] - M);
+            num = fmaf(wt, ks[w].v[row * P + d], num);
+            den = fmaf(wt, ml[w][1][row], den);
+        }
+        o[((size_t)(b * S + q0 + row) * a + h) * D + d] = num / den;
+    }
 }
 
-// dQ of one (token, head): sum over visible keys of dS K, scaled, rotated back.
+// Rotates the pair (x1, x2) = (dim i, dim i + D/2) back by the position's angle.
+__device__ __forceinline__ void rope_back(float2 cs, float& x1, float& x2) {
+    const float y1 = x1 * cs.x + x2 * cs.y, y2 = x2 * cs.x - x1 * cs.y;
+    x1 = y1;
+    x2 = y2;
+}
+
+// dQ, and on the way the row statistics that dK, dV need: the log-sum-exp of the scaled
+// scores (a first sweep over the keys) and D.
 template <int D>
-__global__ __launch_bounds__(64) void dq_f32_kernel(const float* __restrict__ q, const float* __restrict__ kc,
-                                                    const float* __restrict__ vc, const float* __restrict__ dO,
-                                                    const float* __restrict__ lse, const float* __restrict__ dsum,
-                                                    const float2* __restrict__ rope, float* __restrict__ out,
-                                                    int ldo, int B, int S, int a, int g, int cap) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * S * a) return;
-    const int r = idx / a, h = idx - r * a, kvh = h / (a / g);
-    const int b = r / S, pos = r - b * S;
+__global__ __launch_bounds__(256) void dq_f32_kernel(AttnBwdF32 A) {
+    constexpr int P = F32Tile<D>::P, N4 = D / 16, HALF = D / 2;
+    __shared__ F32Tile<D> qs, ds, ks[4], vs[4];
+    __shared__ float ps[4][FT][FT + 1], ml[4][2][FT], lse_s[FT], dsum_s[FT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane >> 2, c = lane & 3;
+    const int S = A.S, a = A.a, nqt = (S + FT - 1) / FT;
+    const int qt = nqt - 1 - blockIdx.x / (A.B * a), bh = blockIdx.x % (A.B * a);
+    const int b = bh / a, h = bh - b * a, kvh = h / (a / A.g);
+    const int q0 = qt * FT, nq = min(S - q0, FT);
     const float scale = 1.0f / sqrtf((float)D);
-    const float* qr = q + ((size_t)r * a + h) * D;
-    const float* dor = dO + ((size_t)r * a + h) * D;
-    const float* kb = kc + ((size_t)b * g + kvh) * cap * D;
-    const float* vb = vc + ((size_t)b * g + kvh) * D * cap;
-    float acc[D];
-    for (int i = 0; i < D; ++i) acc[i] = 0.f;
-    const float L = lse[idx], Dd = dsum[idx];
-    for (int t = 0; t <= pos; ++t) {
-        float s = 0.f, dp = 0.f;
-        for (int i = 0; i < D; ++i) {
-            s = fmaf(qr[i], kb[(size_t)t * D + i], s);
-            dp = fmaf(dor[i], vb[(size_t)i * cap + t], dp);
-        }
-        const float ds = expf(s * scale - L) * (dp - Dd);
-        for (int i = 0; i < D; ++i) acc[i] = fmaf(ds, kb[(size_t)t * D + i], acc[i]);
+    const float* kb = A.kc + ((size_t)b * A.g + kvh) * A.cap * D;
+    const float* vb = A.vc + ((size_t)b * A.g + kvh) * D * A.cap;
+    const size_t row0 = ((size_t)(b * S + q0) * a + h) * D;
+    {
+        RowLoad<D, 256> x, y;
+        x.load(A.q + row0, (size_t)a * D, nq, tid);
+        y.load(A.dO + row0, (size_t)a * D, nq, tid);
+        x.store(qs, tid);
+        y.store(ds, tid);
     }
-    const int half = D / 2;
-    float* o = out + (size_t)r * ldo + h * D;
-    for (int i = 0; i < half; ++i) {
-        const float2 cs = rope[(size_t)pos * half + i];
-        const float x1 = acc[i] * scale, x2 = acc[i + half] * scale;
-        o[i] = x1 * cs.x + x2 * cs.y;
-        o[i + half] = x2 * cs.x - x1 * cs.y;
+    __syncthreads();
+    {
+        const int row = tid >> 4, sub = tid & 15;
+        float t = 0.f;
+        if (row < nq)
+            for (int d = sub; d < D; d += 16) t = fmaf(ds.v[row * P + d], A.O[row0 + (size_t)row * a * D + d], t);
+#pragma unroll
+        for (int k = 8; k >= 1; k >>= 1) t += __shfl_xor(t, k);
+        if (sub == 0) dsum_s[row] = t;
+    }
+    const int lim0 = min(q0 + r, S - 1);
+    auto visible = [&](int t) { return lim0 - t * FT; };   // last visible key of the row in tile t
+    float m = -INFINITY, l = 0.f;
+    RowLoad<D, 64> kl;
+    ColLoad<D, 64> vl;
+    auto fetch_k = [&](int t) { kl.load(kb + (size_t)t * FT * D, D, min(S - t * FT, FT), lane); };
+    auto fetch_v = [&](int t) { vl.load(vb + t * FT, A.cap, min(S - t * FT, FT), lane); };
+    if (wave <= qt) fetch_k(wave);
+    for (int t = wave; t <= qt; t += 4) {
+        wave_sync();
+        kl.store(ks[wave], lane);
+        if (t + 4 <= qt) fetch_k(t + 4);
+        wave_sync();
+        float s[4];
+        dot_tile<D>(qs, ks[wave], r, c, s);
+        const int lim = visible(t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = 4 * c + e <= lim ? s[e] * scale : -INFINITY;
+        softmax_step(s, m, l);
+    }
+    if (wave <= qt) {
+        fetch_k(wave);
+        fetch_v(wave);
+    }
+    if (c == 0) {
+        ml[wave][0][r] = m;
+        ml[wave][1][r] = l;
+    }
+    __syncthreads();
+    if (tid < FT) {
+        const float M = fmaxf(fmaxf(ml[0][0][tid], ml[1][0][tid]), fmaxf(ml[2][0][tid], ml[3][0][tid]));
+        float den = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) den = fmaf(expf(ml[w][0][tid] - M), ml[w][1][tid], den);
+        const float lse = M + logf(den);
+        lse_s[tid] = lse;
+        if (tid < nq) {
+            const size_t i = (size_t)(b * S + q0 + tid) * a + h;
+            A.lse[i] = lse;
+            A.dsum[i] = dsum_s[tid];
+        }
+    }
+    __syncthreads();
+    const float lse = lse_s[r], dd = dsum_s[r];
+    f32x4 acc[N4];
+#pragma unroll
+    for (int i = 0; i < N4; ++i) acc[i] = f32x4{};
+    for (int t = wave; t <= qt; t += 4) {
+        wave_sync();
+        kl.store(ks[wave], lane);
+        vl.store(vs[wave], lane);
+        if (t + 4 <= qt) {
+            fetch_k(t + 4);
+            fetch_v(t + 4);
+        }
+        wave_sync();
+        float s[4], dp[4];
+        dot_tile<D>(qs, ks[wave], r, c, s);
+        dot_tile<D>(ds, vs[wave], r, c, dp);
+        const int lim = visible(t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ps[wave][r][4 * c + e] = expf(s[e] * scale - lse) * (dp[e] - dd);
+        wave_sync();
+        for (int j = 0; j < FT; ++j)
+            if (j <= lim) add_row<D>(acc, ks[wave], j, c, ps[wave][r][j]);
+    }
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < N4; ++i) *(f32x4*)&ks[wave].v[r * P + 16 * i + 4 * c] = acc[i];
+    __syncthreads();
+    for (int id = tid; id < FT * HALF; id += 256) {
+        const int row = id / HALF, i = id % HALF;
+        if (row >= nq) continue;
+        float x1 = 0.f, x2 = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            x1 += ks[w].v[row * P + i];
+            x2 += ks[w].v[row * P + i + HALF];
+        }
+        x1 *= scale;
+        x2 *= scale;
+        rope_back(A.rope[(size_t)(q0 + row) * HALF + i], x1, x2);
+        float* dst = A.out_q + (size_t)(b * S + q0 + row) * A.ldo + h * D;
+        dst[i] = x1;
+        dst[i + HALF] = x2;
     }
 }
 
-// dK, dV of one (sequence, KV head, key): sum over the later queries of the r heads.
+// dK, dV of 16 keys: the sum over the r query heads and the query tiles at or after them.
 template <int D>
-__global__ __launch_bounds__(64) void dkv_f32_kernel(const float* __restrict__ q, const float* __restrict__ kc,
-                                                     const float* __restrict__ vc, const float* __restrict__ dO,
-                                                     const float* __restrict__ lse, const float* __restrict__ dsum,
-                                                     const float2* __restrict__ rope,
-                                                     const float* acc_in_k, const float* acc_in_v,
-                                                     float* acc_out_k, float* acc_out_v, float* __restrict__ out,
-                                                     int ldo, int col_k, int col_v, int B, int S, int a, int g,
-                                                     int cap) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * g * S) return;
-    const int key = idx % S, bk = idx / S, b = bk / g, kvh = bk - b * g;
-    const int r = a / g;
+__global__ __launch_bounds__(256) void dkv_f32_kernel(AttnBwdF32 A) {
+    constexpr int P = F32Tile<D>::P, N4 = D / 16, HALF = D / 2;
+    __shared__ F32Tile<D> ks, vs, qs[4], ds[4];
+    __shared__ float ps[4][FT][FT + 1], dss[4][FT][FT + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane >> 2, c = lane & 3;
+    const int S = A.S, a = A.a, g = A.g, rep = a / g, nqt = (S + FT - 1) / FT;
+    const int kt = blockIdx.x / (A.B * g), bk = blockIdx.x % (A.B * g);   // most query tiles first
+    const int b = bk / g, kvh = bk - b * g;
+    const int k0 = kt * FT, nk = min(S - k0, FT);
     const float scale = 1.0f / sqrtf((float)D);
-    const float* kr = kc + (((size_t)b * g + kvh) * cap + key) * D;
-    const float* vb = vc + ((size_t)b * g + kvh) * D * cap;
-    float vk[D], dk[D], dv[D];
-    for (int i = 0; i < D; ++i) {
-        vk[i] = vb[(size_t)i * cap + key];
-        dk[i] = 0.f;
-        dv[i] = 0.f;
+    {
+        RowLoad<D, 256> x;
+        ColLoad<D, 256> y;
+        x.load(A.kc + (((size_t)b * g + kvh) * A.cap + k0) * D, D, nk, tid);
+        y.load(A.vc + ((size_t)b * g + kvh) * D * A.cap + k0, A.cap, nk, tid);
+        x.store(ks, tid);
+        y.store(vs, tid);
     }
-    for (int j = kvh * r; j < (kvh + 1) * r; ++j)
-        for (int t = key; t < S; ++t) {
-            const size_t qi = ((size_t)(b * S + t) * a + j);
-            const float* qr = q + qi * D;
-            const float* dor = dO + qi * D;
-            float s = 0.f, dp = 0.f;
-            for (int i = 0; i < D; ++i) {
-                s = fmaf(qr[i], kr[i], s);
-                dp = fmaf(dor[i], vk[i], dp);
-            }
-            const float p = expf(s * scale - lse[qi]);
-            const float ds = p * (dp - dsum[qi]);
-            for (int i = 0; i < D; ++i) {
-                dv[i] = fmaf(p, dor[i], dv[i]);
-                dk[i] = fmaf(ds, qr[i], dk[i]);
-            }
+    __syncthreads();
+    f32x4 dk[N4], dv[N4];
+#pragma unroll
+    for (int i = 0; i < N4; ++i) dk[i] = dv[i] = f32x4{};
+    const int per = nqt - kt, n = rep * per;      // query tiles per head, all
+    RowLoad<D, 64> ql, dl;
+    float lse_n = 0.f, dd_n = 0.f;                // of the lane's row, next tile
+    auto fetch = [&](int it) {
+        const int h = kvh * rep + it / per, q0 = (kt + it % per) * FT, nq = min(S - q0, FT);
+        const size_t row0 = ((size_t)(b * S + q0) * a + h) * D;
+        ql.load(A.q + row0, (size_t)a * D, nq, lane);
+        dl.load(A.dO + row0, (size_t)a * D, nq, lane);
+        const size_t i = (size_t)(b * S + q0 + min(r, nq - 1)) * a + h;
+        lse_n = A.lse[i];
+        dd_n = A.dsum[i];
+    };
+    if (wave < n) fetch(wave);
+    for (int it = wave; it < n; it += 4) {
+        const int q0 = (kt + it % per) * FT, nq = min(S - q0, FT);
+        const float lse = lse_n, dd = dd_n;
+        wave_sync();
+        ql.store(qs[wave], lane);
+        dl.store(ds[wave], lane);
+        if (it + 4 < n) fetch(it + 4);
+        wave_sync();
+        float s[4], dp[4];
+        dot_tile<D>(qs[wave], ks, r, c, s);
+        dot_tile<D>(ds[wave], vs, r, c, dp);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float p = expf(s[e] * scale - lse);
+            ps[wave][r][4 * c + e] = p;
+            dss[wave][r][4 * c + e] = p * (dp[e] - dd);
         }
-    const int half = D / 2;
-    const size_t ai = idx * (size_t)D;          // [B][g][S][D]
-    for (int i = 0; i < half; ++i) {
-        const float2 cs = rope[(size_t)key * half + i];
-        const float x1 = dk[i] * scale, x2 = dk[i + half] * scale;
-        dk[i] = x1 * cs.x + x2 * cs.y;
-        dk[i + half] = x2 * cs.x - x1 * cs.y;
+        wave_sync();
+        // The lane's key is k0 + r: queries q0 + j >= it, below S.
+        for (int j = 0; j < nq; ++j)
+            if (q0 + j >= k0 + r) {
+                add_row<D>(dv, ds[wave], j, c, ps[wave][j][r]);
+                add_row<D>(dk, qs[wave], j, c, dss[wave][j][r]);
+            }
     }
-    for (int i = 0; i < D; ++i) {
-        float yk = dk[i], yv = dv[i];
-        if (acc_in_k) {
-            yk += acc_in_k[ai + i];
-            yv += acc_in_v[ai + i];
-        }
-        if (acc_out_k) {
-            acc_out_k[ai + i] = yk;
-            acc_out_v[ai + i] = yv;
-        }
-        if (out) {
-            float* row = out + (size_t)(b * S + key) * ldo + kvh * D;
-            row[col_k + i] = yk;
-            row[col_v + i] = yv;
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+        *(f32x4*)&qs[wave].v[r * P + 16 * i + 4 * c] = dk[i];
+        *(f32x4*)&ds[wave].v[r * P + 16 * i + 4 * c] = dv[i];
+    }
+    __syncthreads();
+    for (int id = tid; id < FT * HALF; id += 256) {
+        const int row = id / HALF, i = id % HALF, key = k0 + row;
+        if (row >= nk) continue;
+        float yk[2] = {0.f, 0.f}, yv[2] = {0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int z = 0; z < 2; ++z) {
+                yk[z] += qs[w].v[row * P + i + z * HALF];
+                yv[z] += ds[w].v[row * P + i + z * HALF];
+            }
+        yk[0] *= scale;
+        yk[1] *= scale;
+        rope_back(A.rope[(size_t)key * HALF + i], yk[0], yk[1]);
+        const size_t ai = (((size_t)b * g + kvh) * S + key) * D;
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            const int d = i + z * HALF;
+            if (A.acc_in_k) {
+                yk[z] += A.acc_in_k[ai + d];
+                yv[z] += A.acc_in_v[ai + d];
+            }
+            if (A.acc_out_k) {
+                A.acc_out_k[ai + d] = yk[z];
+                A.acc_out_v[ai + d] = yv[z];
+            }
+            if (A.out_kv) {
+                float* out = A.out_kv + (size_t)(b * S + key) * A.ldo + kvh * D;
+                out[A.col_k + d] = yk[z];
+                out[A.col_v + d] = yv[z];
+            }
         }
     }
 }
 
 }  // namespace
 
-hipError_t gemm_f32_strided(const float* a, size_t sam, size_t sak, const float* b, size_t sbk, size_t sbn,
-                            const float* res, float* c, size_t ldc, int M, int N, int K, hipStream_t st) {
-    if (M < 1 || N < 1) return hipSuccess;
-    hipLaunchKernelGGL(gemm_f32s_kernel, dim3((N + 63) / 64, (M + 3) / 4), dim3(256), 0, st, a, sam, sak, b, sbk,
-                       sbn, res, c, ldc, M, N, K);
+hipError_t attn_seq_f32(const float* q, const float* kc, const float* vc, float* o, int B, int S, int a, int g, int d,
+                        int cap, hipStream_t st) {
+    const dim3 grid((S + FT - 1) / FT * B * a), block(256);
+    switch (d) {
+        case 16: hipLaunchKernelGGL(attn_tile_f32_kernel<16>, grid, block, 0, st, q, kc, vc, o, B, S, a, g, cap); break;
+        case 32: hipLaunchKernelGGL(attn_tile_f32_kernel<32>, grid, block, 0, st, q, kc, vc, o, B, S, a, g, cap); break;
+        case 64: hipLaunchKernelGGL(attn_tile_f32_kernel<64>, grid, block, 0, st, q, kc, vc, o, B, S, a, g, cap); break;
+        case 128: hipLaunchKernelGGL(attn_tile_f32_kernel<128>, grid, block, 0, st, q, kc, vc, o, B, S, a, g, cap); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
 hipError_t attn_bwd_f32(const AttnBwdF32& p, hipStream_t st) {
-    const int nq_items = p.B * p.S * p.a, nk_items = p.B * p.g * p.S;
-    const dim3 gq((nq_items + 63) / 64), gk((nk_items + 63) / 64), blk(64);
-#define KVP_BWD_F32(DD)                                                                                            \
-    hipLaunchKernelGGL(stats_f32_kernel<DD>, gq, blk, 0, st, p.q, p.kc, p.dO, p.O, p.lse, p.dsum, p.B, p.S, p.a,   \
-                       p.g, p.cap);                                                                                \
-    hipLaunchKernelGGL(dkv_f32_kernel<DD>, gk, blk, 0, st, p.q, p.kc, p.vc, p.dO, p.lse, p.dsum, p.rope,           \
-                       p.acc_in_k, p.acc_in_v, p.acc_out_k, p.acc_out_v, p.out_kv, p.ldo, p.col_k, p.col_v, p.B,   \
-                       p.S, p.a, p.g, p.cap);                                                                      \
-    hipLaunchKernelGGL(dq_f32_kernel<DD>, gq, blk, 0, st, p.q, p.kc, p.vc, p.dO, p.lse, p.dsum, p.rope, p.out_q,   \
-                       p.ldo, p.B, p.S, p.a, p.g, p.cap)
+    const int nt = (p.S + FT - 1) / FT;
+    const dim3 gq(nt * p.B * p.a), gk(nt * p.B * p.g), block(256);
+#define KVP_BWD_F32(DD)                                                  \
+    hipLaunchKernelGGL(dq_f32_kernel<DD>, gq, block, 0, st, p);          \
+    hipLaunchKernelGGL(dkv_f32_kernel<DD>, gk, block, 0, st, p)
     switch (p.d) {
         case 16: KVP_BWD_F32(16); break;
         case 32: KVP_BWD_F32(32); break;

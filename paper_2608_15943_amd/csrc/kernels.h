@@ -189,17 +189,25 @@ hipError_t rope_scatter(const float* proj, int nsplit, size_t split_stride, int 
 hipError_t gemm_f32(const float* a, const WRows& w, int M, int N, int K, float* out,
                     const float* x_res, hipStream_t st);
 
-// Attention for fp32 models: row r of q [rows][a*d] is sequence r / S at
-// position r % S (lens == nullptr) or sequence r at lens[r]; attends [0, pos].
+// Attention for fp32 models, one query per sequence: row r of q [rows][a*d] at position
+// lens[r]; attends [0, lens[r]].
 hipError_t attn_f32(const float* q, const float* kc, const float* vc, const int32_t* lens,
-                    float* o, int rows, int S, int a, int g, int d, int cap, hipStream_t st);
+                    float* o, int rows, int a, int g, int d, int cap, hipStream_t st);
+// The same over whole sequences: q [B*S][a*d], causal.
+hipError_t attn_seq_f32(const float* q, const float* kc, const float* vc, float* o, int B, int S, int a, int g, int d,
+                        int cap, hipStream_t st);
 
 // ---- fp32 backward (vector ALU) ---------------------------------------------
 
-// C[m][n] = R[m][n] + sum_k A(m, k) B(k, n) with A(m, k) = a[m * sam + k * sak] and
-// B(k, n) = b[k * sbk + n * sbn]; R = res (row stride ldc, may equal c) or 0 when null.
-hipError_t gemm_f32_strided(const float* a, size_t sam, size_t sak, const float* b, size_t sbk, size_t sbn,
-                            const float* res, float* c, size_t ldc, int M, int N, int K, hipStream_t st);
+// c[m][n] = res[m][n] + sum_k a[m][k] b[k][n]: a row stride lda, the rows of b (stride ldb)
+// stacked along k from up to three buffers, res and c row stride ldc (res may be c, or null
+// for 0).
+hipError_t gemm_f32_nn(const float* a, size_t lda, const WRows& b, size_t ldb, const float* res, float* c, size_t ldc,
+                       int M, int N, int K, hipStream_t st);
+// C[m][n] = sum_k a[k][m] b[k][n]; C's rows go to c[0] (rows[0] of them), then c[1], c[2],
+// N floats each.
+hipError_t gemm_f32_tn(const float* a, size_t lda, const float* b, size_t ldb, float* const c[3], const int rows[3],
+                       int M, int N, int K, hipStream_t st);
 
 // Attention backward of one fp32 layer: q, dO, O [B*S][a*d] (q after RoPE), the producer's
 // K slot [B][g][cap][d] and V slot [B][g][d][cap]; lse and dsum [B*S*a] are scratch.

@@ -331,9 +331,8 @@ int run_prefill_layer(kvp_ctx* c, int l, const LayerIO& io, void* o_buf, char* w
          })))
         return rc;
     if ((rc = timed(c, KVP_K_F32_ATTN, st, [&] {
-             return check_hip(kvp::attn_f32(q, (const float*)P.kc, (const float*)P.vc, nullptr,
-                                            (float*)o_buf, M, S, c->d.a, c->d.g, c->d.d_h,
-                                            c->d.kv_capacity, st),
+             return check_hip(kvp::attn_seq_f32(q, (const float*)P.kc, (const float*)P.vc, (float*)o_buf, B, S,
+                                                c->d.a, c->d.g, c->d.d_h, c->d.kv_capacity, st),
                               "attention (fp32)");
          })))
         return rc;
@@ -430,7 +429,7 @@ int run_decode_layer(kvp_ctx* c, int l, const LayerIO& io, const int32_t* lens,
     }
     if ((rc = timed(c, KVP_K_F32_ATTN, st, [&] {
              return check_hip(kvp::attn_f32((const float*)q, (const float*)P.kc, (const float*)P.vc,
-                                            lens, (float*)o, B, 0, c->d.a, c->d.g, c->d.d_h,
+                                            lens, (float*)o, B, c->d.a, c->d.g, c->d.d_h,
                                             c->d.kv_capacity, st),
                               "decode attention (fp32)");
          })))
@@ -1023,14 +1022,15 @@ int backward_f32(kvp_ctx* ctx, const float* x, const float* dy, float* dx, int B
         const float* G = l == L - 1 ? dy : dx;
         // dO = G W_O, dW_O = G^T O.
         if ((rc = gemm([&] {
-                 return check_hip(kvp::gemm_f32_strided(G, h, 1, (const float*)Ly.wo, nq, 1, nullptr, dO, nq, M,
-                                                        nq, h, st),
+                 return check_hip(kvp::gemm_f32_nn(G, h, kvp::WRows{{Ly.wo, nullptr, nullptr}, {h, 0, 0}}, nq, nullptr,
+                                                   dO, nq, M, nq, h, st),
                                   "dO GEMM (fp32)");
              })))
             return rc;
+        float* const wo_dst[3] = {Ly.dwo, nullptr, nullptr};
+        const int wo_rows[3] = {h, 0, 0};
         if ((rc = gemm([&] {
-                 return check_hip(kvp::gemm_f32_strided(G, 1, h, Ol, nq, 1, nullptr, Ly.dwo, nq, h, nq, M, st),
-                                  "dW_O GEMM (fp32)");
+                 return check_hip(kvp::gemm_f32_tn(G, h, Ol, nq, wo_dst, wo_rows, h, nq, M, st), "dW_O GEMM (fp32)");
              })))
             return rc;
         // Attention: dQ into dqkv; dK, dV into the producer's sums (consumer) or dqkv (producer).
@@ -1059,31 +1059,18 @@ int backward_f32(kvp_ctx* ctx, const float* x, const float* dy, float* dx, int B
                  return check_hip(kvp::attn_bwd_f32(a, st), "attention backward (fp32)");
              })))
             return rc;
-        // dW_Q (, dW_K, dW_V) = [dQ | dK | dV]^T X_l; dX_l = G + dQ W_Q (+ dK W_K + dV W_V).
-        struct Part {
-            int col, rows;
-            const void* wt;
-            float* dw;
-        };
-        const Part parts[3] = {{0, nq, Ly.wq, Ly.dwq}, {nq, nkv, Ly.wk, Ly.dwk}, {nq + nkv, nkv, Ly.wv, Ly.dwv}};
-        for (int i = 0; i < (producer ? 3 : 1); ++i) {
-            const Part& pt = parts[i];
-            if ((rc = gemm([&] {
-                     return check_hip(kvp::gemm_f32_strided(dqkv + pt.col, 1, np, Xl, h, 1, nullptr, pt.dw, h,
-                                                            pt.rows, h, M, st),
-                                      "dW_QKV GEMM (fp32)");
-                 })))
-                return rc;
-        }
-        for (int i = 0; i < (producer ? 3 : 1); ++i) {
-            const Part& pt = parts[i];
-            if ((rc = gemm([&] {
-                     return check_hip(kvp::gemm_f32_strided(dqkv + pt.col, np, 1, (const float*)pt.wt, h, 1,
-                                                            i == 0 ? G : dx, dx, h, M, h, pt.rows, st),
-                                      "dX GEMM (fp32)");
-                 })))
-                return rc;
-        }
+        // dW_Q (, dW_K, dW_V) = [dQ | dK | dV]^T X_l; dX_l = G + [dQ | dK | dV] [W_Q; W_K; W_V].
+        float* const w_dst[3] = {Ly.dwq, Ly.dwk, Ly.dwv};
+        const int w_rows[3] = {nq, producer ? nkv : 0, producer ? nkv : 0};
+        if ((rc = gemm([&] {
+                 return check_hip(kvp::gemm_f32_tn(dqkv, np, Xl, h, w_dst, w_rows, np, h, M, st), "dW_QKV GEMM (fp32)");
+             })))
+            return rc;
+        if ((rc = gemm([&] {
+                 return check_hip(kvp::gemm_f32_nn(dqkv, np, proj_rows(ctx, l, producer), h, G, dx, h, M, h, np, st),
+                                  "dX GEMM (fp32)");
+             })))
+            return rc;
     }
     return ok();
 }

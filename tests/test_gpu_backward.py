@@ -275,3 +275,15 @@ def test_backward_ignores_unwritten_slot_contents():
         assert bool(torch.isfinite(v.float()).all().item()), i
         assert torch.equal(u, v), i
     say("  bit-identical")
+
+
+@pytest.mark.parametrize("h,a,g,d,tau,B,S", [
+    (256, 2, 2, 128, [0, 0], 1, 16),         # one full 16 x 16 tile
+    (256, 2, 1, 128, [0], 1, 17),            # one row past a tile
+    (32, 2, 1, 16, [0, 1], 3, 79),           # five tiles of queries: one wave takes a second tile
+    (1024, 8, 4, 128, [0, 0], 4, 260),       # products that fill the chip (64 x 64 tiles)
+    (48, 3, 1, 16, [0, 0], 2, 33),           # a width that is no multiple of 32
+])
+def test_backward_fp32_over_the_tile_sizes(h, a, g, d, tau, B, S):
+    w = small_workload(f"bwd32t-h{h}-a{a}-g{g}-d{d}", len(tau), h, a, g, tau, dtype="fp32", d_h=d, seed=29)
+    _train_case(w, B, S, S + 1)
