@@ -11,7 +11,7 @@
 //
 // Kernels:
 //   attn_bwd_prep    D = rowsum(dO * O) per (token, head).
-//   transpose_bf16   weight transposes for the dO and dX products.
+//   transpose_bf16   operands of the dO, dX and weight-gradient products.
 //   flash_bwd_kv     one workgroup per (sequence, KV head, 256 keys); loops over the r
 //                    query heads of the group and the query blocks at or after its
 //                    keys; dK, dV accumulate in registers.
@@ -111,38 +111,22 @@ __device__ __forceinline__ bf16x8 pack8(const float* e) {
     return as_bf16x8(w);
 }
 
-// out[c][r] = in[r][c]: 64 x 64 tiles through LDS (weights, once per layer).
-__global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restrict__ in,
-                                                        uint16_t* __restrict__ out, int R, int C,
-                                                        size_t in_ld, size_t out_ld) {
-    __shared__ uint16_t t[64][66];
-    const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int r = r0 + ty + 4 * k, c = c0 + tx;
-        t[ty + 4 * k][tx] = (r < R && c < C) ? in[(size_t)r * in_ld + c] : (uint16_t)0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int c = c0 + ty + 4 * k, r = r0 + tx;
-        if (c < C && r < R) out[(size_t)c * out_ld + r] = t[tx][ty + 4 * k];
-    }
-}
-
-// The same for R, C multiples of 64 and 16-byte aligned rows: 16-byte global accesses (a
-// lane reads 8 elements of a row and writes 8 of a transposed row).
-__global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __restrict__ in,
-                                                          uint16_t* __restrict__ out, size_t in_ld,
-                                                          size_t out_ld) {
+// A 64 x 64 tile of one of the jobs: 16-byte global accesses (a lane reads 8 elements of a row
+// and writes 8 of a transposed row).  One launch for all transposes of a step: each alone is
+// 5 us for a few MB, most of it latency.
+__global__ __launch_bounds__(256) void transpose_kernel(Transposes T) {
     __shared__ uint16_t t[64][65];
-    const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    int j = 0;
+    while (j + 1 < T.n && (int)blockIdx.x >= T.first[j + 1]) ++j;
+    const Transposes::Job& J = T.job[j];
+    const int id = blockIdx.x - T.first[j], nr = (J.R + 63) / 64;
+    const int r0 = id % nr * 64, c0 = id / nr * 64;
     const int tid = threadIdx.x, seg = tid & 7, row = tid >> 3;   // 8 lanes per 64-element row
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int r = row + 32 * k;
-        const u32x4 v = *(const u32x4*)(in + (size_t)(r0 + r) * in_ld + c0 + 8 * seg);
+        u32x4 v = {0, 0, 0, 0};
+        if (r0 + r < J.R) v = *(const u32x4*)(J.in + (size_t)(r0 + r) * J.in_ld + c0 + 8 * seg);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             t[r][8 * seg + 2 * e] = (uint16_t)(v[e] & 0xFFFFu);
@@ -157,7 +141,7 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             v[e] = (uint32_t)t[8 * seg + 2 * e][c] | ((uint32_t)t[8 * seg + 2 * e + 1][c] << 16);
-        *(u32x4*)(out + (size_t)(c0 + c) * out_ld + r0 + 8 * seg) = v;
+        *(u32x4*)(J.out + (size_t)(c0 + c) * J.out_ld + r0 + 8 * seg) = v;
     }
 }
 
@@ -253,10 +237,21 @@ struct KvArgs {
     int ldo, col_k, col_v;
     int B, S, Sp, a, g, cap;
     float scale_log2, scale;
+    int chunk;              // 0, or query blocks per workgroup: sums go to part, see kv_reduce
+    float* part;
 };
 
 constexpr int KV_BQ = 64, KV_BK = 256, KV_NT = 512;
+constexpr size_t kKvSlot = (size_t)2 * KV_BK * D;   // floats a workgroup of a split launch writes
 
+// Query blocks (of all r heads) that key block kb meets.
+__host__ __device__ __forceinline__ int kv_blocks(int kb, int Sp, int r) {
+    const int nqb = Sp / KV_BQ, lo = kb * (KV_BK / KV_BQ);
+    return r * (nqb > lo ? nqb - lo : 0);
+}
+
+// SPLIT: the launch deals chunks of the query blocks (A.chunk) to several workgroups.
+template <bool SPLIT>
 __global__ __launch_bounds__(KV_NT, 2) void flash_bwd_kv_kernel(KvArgs A) {
     __shared__ u32x4 lvt[D * 32];              // V^T of the workgroup's keys, 512-byte rows
     __shared__ u32x4 lq[2][KV_BQ * 16];
@@ -265,10 +260,19 @@ __global__ __launch_bounds__(KV_NT, 2) void flash_bwd_kv_kernel(KvArgs A) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, hi = lane >> 5;
-    const int G = A.B * A.g;
-    const int kb = blockIdx.x / G, grp = blockIdx.x - kb * G;   // heaviest key blocks first
+    const int G = A.B * A.g, r = A.a / A.g;
+    int kb = blockIdx.x / G, slice = 0;         // heaviest key blocks first
+    const int grp = blockIdx.x - kb * G;
+    if constexpr (SPLIT) {
+        // Workgroups of a split launch: ceil(blocks / chunk) of them per key block and group.
+        slice = kb;
+        for (kb = 0;; ++kb) {
+            const int n = (kv_blocks(kb, A.Sp, r) + A.chunk - 1) / A.chunk;
+            if (slice < n) break;
+            slice -= n;
+        }
+    }
     const int b = grp / A.g, kvh = grp - b * A.g;
-    const int r = A.a / A.g;
     const int k0w = kb * KV_BK + 32 * wave;
     const int k0u = __builtin_amdgcn_readfirstlane(k0w);   // the same value, held as wave-uniform
     const int key = k0w + l32;                 // the key whose column this lane holds
@@ -299,7 +303,8 @@ __global__ __launch_bounds__(KV_NT, 2) void flash_bwd_kv_kernel(KvArgs A) {
     const int nqb = A.Sp / KV_BQ;
     const int qb_lo = min(kb * (KV_BK / KV_BQ), nqb);
     const int nq_h = nqb - qb_lo;               // query blocks per head
-    const int n_it = r * nq_h;
+    const int it0 = SPLIT ? slice * A.chunk : 0;
+    const int n_it = SPLIT ? min(r * nq_h, it0 + A.chunk) : r * nq_h;   // one past the last block
     const size_t ld = (size_t)A.a * D;
 
     auto issue = [&](int it, int stg) {
@@ -336,7 +341,7 @@ __global__ __launch_bounds__(KV_NT, 2) void flash_bwd_kv_kernel(KvArgs A) {
     const uint32_t av_lo = (uint32_t)(uintptr_t)((const char*)lvt + wave * (D * 64) + sub_off<D>(tr_row, tr_col)),
                    av_up = (uint32_t)(uintptr_t)((const char*)lvt + wave * (D * 64) + sub_off<D>(tr_row + 4, tr_col));
 
-    if (n_it > 0) issue(0, 0);
+    if (n_it > it0) issue(it0, 0);
     // Per-lane LDS addresses in stage 0 (stage 1 is a constant offset further: the loop below
     // takes the stage as a compile-time constant): the two transposed reads of a dO / Q
     // fragment (row block 0, column block 0), and the lane's Q / dO row chunk (row rsw,
@@ -452,9 +457,22 @@ __global__ __launch_bounds__(KV_NT, 2) void flash_bwd_kv_kernel(KvArgs A) {
         half(std::integral_constant<int, 0>{});
         half(std::integral_constant<int, 1>{});
     };
-    for (int it = 0; it < n_it; it += 2) {
+    for (int it = it0; it < n_it; it += 2) {
         iteration(it, std::integral_constant<int, 0>{});
         if (it + 1 < n_it) iteration(it + 1, std::integral_constant<int, 1>{});
+    }
+    if constexpr (SPLIT) {
+        // This chunk's sums as they are: [dK, dV][256 keys][128] of the workgroup's slot.
+        float* p = A.part + blockIdx.x * kKvSlot + (size_t)(32 * wave + 4 * hi) * D + l32;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                const int off = (8 * (e >> 2) + (e & 3)) * D + 32 * nb;
+                p[off] = dk[nb][e];
+                p[off + KV_BK * D] = dv[nb][e];
+            }
+        return;
     }
 
     // Epilogue: lane column d = 32 nb + l32; register e of block nb holds key
@@ -523,6 +541,71 @@ __global__ __launch_bounds__(KV_NT, 2) void flash_bwd_kv_kernel(KvArgs A) {
         tm_flush(tsk, A.out_t, ldt, A.col_k + kvh * D, t0, A.S - k0w, lane);
         tm_flush(tsv, A.out_t, ldt, A.col_v + kvh * D, t0, A.S - k0w, lane);
     }
+}
+
+// Sums the chunks of a split launch (in order) for 32 keys of one (sequence, KV head), then
+// does what the unsplit epilogue does: scale, rotate dK back, add the consumers' shares, write.
+// Thread: key tid / 8, dims i .. i + 7 and i + 64 .. i + 71 with i = 8 (tid % 8).
+__global__ __launch_bounds__(256) void kv_reduce_kernel(KvArgs A) {
+    __shared__ uint16_t ts[2][D * 32];
+    const int tid = threadIdx.x, G = A.B * A.g, r = A.a / A.g;
+    const int grp = blockIdx.x % G, k0 = blockIdx.x / G * 32, kb = k0 / KV_BK;
+    const int b = grp / A.g, kvh = grp - b * A.g, key = k0 + tid / 8, i0 = 8 * (tid & 7);
+    int first = 0;
+    for (int j = 0; j < kb; ++j) first += (kv_blocks(j, A.Sp, r) + A.chunk - 1) / A.chunk;
+    const int n = (kv_blocks(kb, A.Sp, r) + A.chunk - 1) / A.chunk;
+    if (key < A.S) {
+        f32x4 x[2][2][2] = {};   // [dK, dV][i, i + 64][4 + 4]
+        for (int c = 0; c < n; ++c) {
+            const float* p = A.part + ((size_t)(first + c) * G + grp) * kKvSlot + (size_t)(key % KV_BK) * D + i0;
+#pragma unroll
+            for (int z = 0; z < 2; ++z)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) x[z][h][q] += *(const f32x4*)(p + z * (KV_BK * D) + 64 * h + 4 * q);
+        }
+        const size_t ai = (((size_t)b * A.g + kvh) * A.S + key) * D + i0;
+        float y[2][2][8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float2 cs = A.rope[(size_t)key * 64 + i0 + e];
+            const float x1 = x[0][0][e >> 2][e & 3] * A.scale, x2 = x[0][1][e >> 2][e & 3] * A.scale;
+            y[0][0][e] = x1 * cs.x + x2 * cs.y;
+            y[0][1][e] = x2 * cs.x - x1 * cs.y;
+            y[1][0][e] = x[1][0][e >> 2][e & 3];
+            y[1][1][e] = x[1][1][e >> 2][e & 3];
+        }
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            const float* in = z ? A.acc_in_v : A.acc_in_k;
+            float* acc = z ? A.acc_out_v : A.acc_out_k;
+            const int col = z ? A.col_v : A.col_k;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (in)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) y[z][h][e] += in[ai + 64 * h + e];
+                if (acc)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[ai + 64 * h + e] = y[z][h][e];
+                if (A.out) {
+                    const u32x4 v = __builtin_bit_cast(u32x4, pack8(y[z][h]));
+                    *(u32x4*)(A.out + ((size_t)b * A.S + key) * A.ldo + col + kvh * D + i0 + 64 * h) = v;
+                    if (A.out_t)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            ts[z][(i0 + 64 * h + e) * 32 + tid / 8] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+                }
+            }
+        }
+    }
+    if (!A.out_t) return;
+    __syncthreads();
+    const int wave = tid >> 6;
+    if (wave < 2)
+        tm_flush(ts[wave], A.out_t, (size_t)A.B * A.S, (wave ? A.col_v : A.col_k) + kvh * D, (size_t)b * A.S + k0,
+                 A.S - k0, tid & 63);
 }
 
 // ---------------------------------------------------------------------------
@@ -752,18 +835,46 @@ __global__ __launch_bounds__(Q_NT, 2) void flash_bwd_q_kernel(QArgs A) {
         tm_flush(ts, A.out_t, (size_t)A.B * A.S, head * D, (size_t)b * A.S + q0w, A.S - q0w, lane);
 }
 
+// Workgroups of the dK, dV launch.  One per key block and (sequence, KV head) when that makes
+// two rounds of the 256 CUs or more; else the query blocks (3.4 us each for a workgroup) are
+// dealt in chunks so that about 512 workgroups share them, at least 4 blocks each, and
+// kv_reduce adds the chunks.  Measured at 2 x 777 tokens, 16/8 heads: 64 workgroups of up to
+// 26 blocks took 88 us, 256 of at most 4 take 26 and their sum 16.
+struct KvPlan {
+    int chunk, groups;
+};
+KvPlan kv_plan(int B, int S, int a, int g) {
+    const int Sp = (S + 63) / 64 * 64, r = a / g, nkb = (S + KV_BK - 1) / KV_BK, G = B * g;
+    int64_t blocks = 0;
+    for (int kb = 0; kb < nkb; ++kb) blocks += kv_blocks(kb, Sp, r);
+    if ((int64_t)nkb * G >= 512) return {0, nkb * G};
+    const int chunk = std::max(4, (int)((blocks * G + 511) / 512));
+    if (kv_blocks(0, Sp, r) < 2 * chunk) return {0, nkb * G};
+    int n = 0;
+    for (int kb = 0; kb < nkb; ++kb) n += (kv_blocks(kb, Sp, r) + chunk - 1) / chunk;
+    return {chunk, n * G};
+}
+
 }  // namespace
 
-hipError_t transpose_bf16(const uint16_t* in, uint16_t* out, int R, int C, size_t in_ld, size_t out_ld,
-                          hipStream_t st) {
-    if (R < 1 || C < 1) return hipSuccess;
-    const bool wide = R % 64 == 0 && C % 64 == 0 && in_ld % 8 == 0 && out_ld % 8 == 0 &&
-                      ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    if (wide)
-        hipLaunchKernelGGL(transpose16_kernel, dim3(R / 64, C / 64), dim3(256), 0, st, in, out, in_ld, out_ld);
-    else
-        hipLaunchKernelGGL(transpose_kernel, dim3((R + 63) / 64, (C + 63) / 64), dim3(256), 0, st, in, out, R, C,
-                           in_ld, out_ld);
+size_t bwd_kv_part_floats(int B, int S, int a, int g) {
+    const KvPlan p = kv_plan(B, S, a, g);
+    return p.chunk ? p.groups * kKvSlot : 0;
+}
+
+hipError_t transpose_bf16(Transposes t, hipStream_t st) {
+    int n = 0;
+    for (int j = 0; j < t.n; ++j) {
+        const Transposes::Job& J = t.job[j];
+        if (J.R < 1 || J.C % 64 || J.in_ld % 8 || J.out_ld % 8 || J.out_ld < (J.R + 63) / 64 * 64 ||
+            ((reinterpret_cast<uintptr_t>(J.in) | reinterpret_cast<uintptr_t>(J.out)) & 15))
+            return hipErrorInvalidValue;
+        t.first[j] = n;
+        n += (J.R + 63) / 64 * (J.C / 64);
+    }
+    if (n < 1) return hipSuccess;
+    t.first[t.n] = n;
+    hipLaunchKernelGGL(transpose_kernel, dim3(n), dim3(256), 0, st, t);
     return hipGetLastError();
 }
 
@@ -800,8 +911,16 @@ hipError_t flash_bwd_kv_bf16(const AttnBwdKv& p, hipStream_t st) {
     A.B = p.B; A.S = p.S; A.Sp = p.Sp; A.a = p.a; A.g = p.g; A.cap = p.cap;
     A.scale = (float)(1.0 / sqrt((double)D));
     A.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
-    const int nkb = (p.S + KV_BK - 1) / KV_BK;
-    hipLaunchKernelGGL(flash_bwd_kv_kernel, dim3(nkb * p.B * p.g), dim3(KV_NT), 0, st, A);
+    const KvPlan plan = kv_plan(p.B, p.S, p.a, p.g);
+    A.chunk = plan.chunk;
+    A.part = p.part;
+    if (plan.chunk && !p.part) return hipErrorInvalidValue;
+    if (plan.chunk) {
+        hipLaunchKernelGGL(flash_bwd_kv_kernel<true>, dim3(plan.groups), dim3(KV_NT), 0, st, A);
+        hipLaunchKernelGGL(kv_reduce_kernel, dim3((p.S + 31) / 32 * p.B * p.g), dim3(256), 0, st, A);
+    } else {
+        hipLaunchKernelGGL(flash_bwd_kv_kernel<false>, dim3(plan.groups), dim3(KV_NT), 0, st, A);
+    }
     return hipGetLastError();
 }
 

@@ -25,14 +25,13 @@
 #include "common.h"
 #include "gemm_epi.h"
 #include "kernels.h"
-#include "lds_tr.h"
 
 #include <algorithm>
 
 namespace kvp {
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64, NT = 256, GROUP_M = 8;
+constexpr int BM = 256, BN = 256, BK = 64, GROUP_M = 8;
 
 // Word 3 of a raw buffer resource: a valid (32-bit) data format.
 constexpr int kRsrcWord3 = 0x00020000;
@@ -176,15 +175,15 @@ __global__ __launch_bounds__(kBigNT, 2) void gemm_big(const uint16_t* __restrict
     const int l32 = lane & 31, hi = lane >> 5;
 
     const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
-    // With split K, workgroup slot `split` of every tile takes K columns
-    // [split * K / splits, (split + 1) * K / splits); consecutive ids share a slice.
+    // With split K, workgroup slot `split` of every tile takes the 64-wide K tiles
+    // [split * n / splits, (split + 1) * n / splits) of n; consecutive ids share a slice.
     const int lid0 = xcd_remap(blockIdx.x, gridDim.x);
     const int split = __builtin_amdgcn_readfirstlane(lid0 / (ntm * ntn));
     int tm, tn;
     tile_of(lid0 - split * (ntm * ntn), ntm, ntn, GROUP_M, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
-    const int kslice = __builtin_amdgcn_readfirstlane(K / splits);
-    const int kofs = split * kslice, nk = kslice / BK;
+    const int kt0 = __builtin_amdgcn_readfirstlane(split * (K / BK) / splits);
+    const int nk = __builtin_amdgcn_readfirstlane((split + 1) * (K / BK) / splits) - kt0, kofs = kt0 * BK;
     epi.set_split(split);
 
     // Resources of the four half tiles; a half past M has no rows, one past N repeats the first.
@@ -311,8 +310,8 @@ __global__ __launch_bounds__(256, 2) void gemm_small(const uint16_t* __restrict_
     int tm, tn;
     tile_of(lid0 - split * (ntm * ntn), ntm, ntn, GM, tm, tn);
     const int m0 = tm * BM_, n0 = tn * BN_;
-    const int kslice = __builtin_amdgcn_readfirstlane(K / splits);
-    const int kofs = split * kslice, nk = kslice / BK;
+    const int kt0 = __builtin_amdgcn_readfirstlane(split * (K / BK) / splits);
+    const int nk = __builtin_amdgcn_readfirstlane((split + 1) * (K / BK) / splits) - kt0, kofs = kt0 * BK;
     epi.set_split(split);
 
     const __amdgpu_buffer_rsrc_t ra = row_rsrc(A + (size_t)m0 * K, min(M - m0, BM_), K);
@@ -394,153 +393,6 @@ __global__ __launch_bounds__(256, 2) void gemm_small(const uint16_t* __restrict_
     epi.template flush<BM_, BN_, 256>(m0, n0, tid, M, N, st, pre);
 }
 
-// ---------------------------------------------------------------------------
-// 256 x 256 x 64 tiles of 4 waves (128 x 128 each) for C[M][N] = sum_k A[k][m] B[k][n] with both operands given K-major
-// ([K][rows], rows contiguous): the weight gradients dW_O = G^T O and
-// dW_QKV = [dQ|dK|dV]^T X of the backward, whose K is the token axis.  Each operand tile is
-// staged as [64 k][256 rows] in the sub-tiled layout and its MFMA fragments are taken along
-// the tile's rows with the LDS transpose read (two ds_read_b64_tr_b16 each), so neither
-// operand is copied transposed.  Any K: the last tile reads clamped rows, and the A
-// fragments zero the rows past K.  (For products with K-major weights, dO = G W_O and
-// dX += [dQ|dK|dV] W_stack, the row-major kernel on once-transposed weights is faster: the
-// transpose read moves 8 bytes per lane per instruction against 16.)
-// ---------------------------------------------------------------------------
-// A K-major operand: k-rows of `ld` values, stacked from up to three buffers (p[i] holds
-// rows[i] k-rows).  Written this way (templated operand, if-constexpr'd loads) the kernel
-// compiles to 384 registers without spills; a plain single-pointer spelling of the same
-// loop was compiled to 512 registers plus 130-180 spilled ones, 2.6x slower.
-template <bool T>
-struct Operand {
-    WRows w;
-    int ld;
-    __device__ __forceinline__ const uint16_t* krow(int k) const {
-        if (k < w.rows[0]) return (const uint16_t*)w.p[0] + (size_t)k * ld;
-        k -= w.rows[0];
-        if (k < w.rows[1]) return (const uint16_t*)w.p[1] + (size_t)k * ld;
-        k -= w.rows[1];
-        return (const uint16_t*)w.p[2] + (size_t)k * ld;
-    }
-};
-
-template <class Epi, bool TA, bool TB>
-__global__ __launch_bounds__(NT, 1) void gemm_bf16_g(Operand<TA> Aop, Operand<TB> Bop, int M, int N, int K,
-                                                    int splits, Epi epi) {
-    __shared__ u32x4 lds[2][2][BM * 8];  // [stage][A, B]: [64 k][256] bf16, sub-tiled
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, hi = lane >> 5;
-    const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
-    const int lid0 = xcd_remap(blockIdx.x, gridDim.x);
-    const int split = lid0 / (ntm * ntn);
-    const int lid = lid0 - split * (ntm * ntn);
-    epi.set_split(split);
-    const int group = lid / (GROUP_M * ntn), first = group * GROUP_M;
-    const int gsz = min(ntm - first, GROUP_M);
-    const int in_g = lid - group * GROUP_M * ntn;
-    const int m0 = (first + in_g % gsz) * BM, n0 = (in_g / gsz) * BN;
-    const int nkt = (K + BK - 1) / BK;
-    const int kt0 = split * nkt / splits, kt1 = (split + 1) * nkt / splits;
-    const int ch = sub_chunk(lane);
-    auto tsrc = [&](const auto& op, int c0, int C, int kt, int j) {
-        const int u = 8 * wave + j, sb = u >> 2, q = u & 3;
-        const int k = min(kt * BK + 16 * q + (lane >> 2), K - 1);
-        const int col = min(c0 + 32 * sb + 8 * ch, C - 8);
-        return op.krow(k) + col;
-    };
-    auto issue_part = [&](int kt, int stg, int j) {
-        if constexpr (TA) {
-            const int u = 8 * wave + j;
-            __builtin_amdgcn_global_load_lds((gvoid_t*)tsrc(Aop, m0, M, kt, j),
-                                             (lvoid_t*)((char*)&lds[stg][0][0] + (u >> 2) * 4096 + (u & 3) * 1024),
-                                             16, 0, 0);
-        }
-        if constexpr (TB) {
-            const int u = 8 * wave + j;
-            __builtin_amdgcn_global_load_lds((gvoid_t*)tsrc(Bop, n0, N, kt, j),
-                                             (lvoid_t*)((char*)&lds[stg][1][0] + (u >> 2) * 4096 + (u & 3) * 1024),
-                                             16, 0, 0);
-        }
-    };
-    auto issue = [&](int kt, int stg) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) issue_part(kt, stg, j);
-    };
-    f32x16 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
-    const bool ktail = TA && (K % BK) != 0;
-    auto load_frags = [&](int stg, int kt, int ks, bf16x8 (&fa)[4], bf16x8 (&fb)[4]) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (TA) fa[i] = tr_frag<BK, false>(lds[stg][0], 16 * ks, wm * 128 + 32 * i, lane);
-            if constexpr (TB) fb[i] = tr_frag<BK, false>(lds[stg][1], 16 * ks, wn * 128 + 32 * i, lane);
-        }
-        if (ktail && kt == nkt - 1) {
-            const int kb = kt * BK + 16 * ks + 8 * hi;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                u32x4 v = __builtin_bit_cast(u32x4, fa[i]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    v[e] &= (kb + 2 * e < K ? 0x0000FFFFu : 0u) | (kb + 2 * e + 1 < K ? 0xFFFF0000u : 0u);
-                fa[i] = __builtin_bit_cast(bf16x8, v);
-            }
-        }
-    };
-    (void)l32;
-    if (kt0 < kt1) {
-        issue(kt0, 0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        bf16x8 fa[4], fb[4], ga[4], gb[4];
-        load_frags(0, kt0, 0, fa, fb);
-        for (int kt = kt0; kt < kt1; ++kt) {
-            const int cur = (kt - kt0) & 1;
-            const bool more = kt + 1 < kt1;
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                if (more && ks < 2) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) issue_part(kt + 1, cur ^ 1, 4 * ks + j);
-                }
-                if (ks < 3) load_frags(cur, kt, ks + 1, ga, gb);
-#pragma unroll
-                for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                    for (int nb2 = 0; nb2 < 4; ++nb2) acc[mb][nb2] = mfma32x32x16(fa[mb], fb[nb2], acc[mb][nb2]);
-                if (ks < 3) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        fa[i] = ga[i];
-                        fb[i] = gb[i];
-                    }
-                }
-            }
-            if (more) {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
-                load_frags(cur ^ 1, kt + 1, 0, fa, fb);
-            }
-        }
-    }
-    char* st = (char*)&lds[0][0][0];
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {   // rows 128 pass .. + 127: the waves with wm == pass
-        __syncthreads();
-        typename Epi::template Pre<128, BN, NT> pre;
-        epi.template prefetch<128, BN, NT>(m0 + 128 * pass, n0, tid, M, N, pre);
-        if (wm == pass)
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                for (int nb2 = 0; nb2 < 4; ++nb2) st_block<BN>(st, acc[mb][nb2], 32 * mb, wn * 128 + 32 * nb2, lane);
-        __syncthreads();
-        epi.template flush<128, BN, NT>(m0 + 128 * pass, n0, tid, M, N, st, pre);
-    }
-}
-
 // Estimated time (us) of a product on each tile, k = K / 1024, t = number of tiles: fitted to
 // the layer projections at widths 2048, 4096 and 8192 and 64 to 16384 tokens.  A 256 x 256
 // tile has a CU to itself; a round costs 13 + 13.5 k with few CUs busy and 17.5 + 21.7 k with
@@ -549,7 +401,11 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_g(Operand<TA> Aop, Operand<TB
 // Measured (us, 256 / 128 / 64): 200 tokens at width 4096, Q|K|V 73 / 44 / 26; 1024 tokens
 // at 2048, output 40 / 25 / 18; 3000 tokens at 2048, Q|K|V 55 / 59 / 81, output 42 / 33 / 43;
 // 8192 tokens at 8192, Q|K|V 978 / 1217 / 2407.
-int pick_tile(int M, int N, int K, int splits) {
+struct Pick {
+    int tile;
+    float us;
+};
+Pick pick_tile(int M, int N, int K, int splits) {
     const float k = (float)K / (float)splits / 1024.f;
     auto tiles = [&](int b) { return (int64_t)((M + b - 1) / b) * ((N + b - 1) / b) * splits; };
     const int64_t t = tiles(256), rest = t % 256;
@@ -557,15 +413,16 @@ int pick_tile(int M, int N, int K, int splits) {
     if (rest) big += 13.f + 13.5f * k + (float)rest / 256.f * (4.5f + 8.2f * k);
     const float mid = std::max(7.f + 8.8f * k, (float)tiles(128) / 512.f * (9.f + 13.4f * k));
     const float low = std::max(6.5f + 3.5f * k, (float)tiles(64) / 512.f * (8.f + 5.1f * k));
-    if (low < mid && low < big) return 64;
-    return mid < big ? 128 : 256;
+    if (low < mid && low < big) return {64, low};
+    return mid < big ? Pick{128, mid} : Pick{256, big};
 }
 
 template <class Epi>
 hipError_t launch(const uint16_t* A, const WRows& W, int M, int N, int K, const Epi& epi,
                   hipStream_t st, int splits = 1) {
-    if (M < 1 || N % 128 || splits < 1 || K % (BK * splits)) return hipErrorInvalidValue;
-    const int b = pick_tile(M, N, K, splits);
+    if (M < 1 || N % 128 || K % BK || splits < 1 || splits > K / BK)
+        return hipErrorInvalidValue;
+    const int b = pick_tile(M, N, K, splits).tile;
     const dim3 grid(((M + b - 1) / b) * ((N + b - 1) / b) * splits);
     if (b == 64)
         hipLaunchKernelGGL((gemm_small<Epi, 64, 64, 4, 16>), grid, dim3(256), 0, st, A, W, M, N, K, splits, epi);
@@ -590,40 +447,32 @@ hipError_t gemm_resid_bf16(const uint16_t* a, const uint16_t* w, const void* x_r
     return launch(a, W, M, N, K, ResidEpi<false>{x_res, y, yf}, st);
 }
 
-hipError_t gemm_kmajor_out_bf16(const uint16_t* a, int lda, const uint16_t* b, int ldb, int M, int N, int K,
-                                int splits, float* part, hipStream_t st) {
-    if (splits < 1 || splits > (K + BK - 1) / BK || M % 8 || N % 8 || lda % 8 || ldb % 8)
-        return hipErrorInvalidValue;
-    Operand<true> A{{{a, nullptr, nullptr}, {K, 0, 0}}, lda};
-    Operand<true> B{{{b, nullptr, nullptr}, {K, 0, 0}}, ldb};
-    const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    hipLaunchKernelGGL((gemm_bf16_g<OutEpi, true, true>), dim3(tiles * splits), dim3(NT), 0, st, A, B, M, N, K,
-                       splits, OutEpi{part, (size_t)M * N, 0, false});
-    return hipGetLastError();
-}
-
 hipError_t gemm_out_bf16(const uint16_t* a, const uint16_t* w, int M, int N, int K, uint16_t* c,
                          hipStream_t st) {
-    if (K % BK) return hipErrorInvalidValue;
     WRows W{{w, nullptr, nullptr}, {N, 0, 0}};
-    return launch(a, W, M, N, K, OutEpi{c, 0, 0, true}, st);
+    return launch(a, W, M, N, K, OutEpi<true>{c, nullptr, nullptr, M, 0, 0, 0}, st);
 }
 
-hipError_t gemm_nt_out_splits(const uint16_t* a, const uint16_t* w, int M, int N, int K, int splits, float* part,
-                              hipStream_t st) {
-    if (splits < 1 || K % (BK * splits)) return hipErrorInvalidValue;
+hipError_t gemm_out_f32(const uint16_t* a, const uint16_t* w, int M, int N, int K, int splits, float* part, float* dst0,
+                        int rows0, float* dst1, int rows1, float* dst2, hipStream_t st) {
     WRows W{{w, nullptr, nullptr}, {N, 0, 0}};
-    return launch(a, W, M, N, K, OutEpi{part, (size_t)M * N, 0, false}, st, splits);
+    if (splits == 1) return launch(a, W, M, N, K, OutEpi<false>{dst0, dst1, dst2, rows0, rows1, 0, 0}, st);
+    return launch(a, W, M, N, K, OutEpi<false>{part, nullptr, nullptr, M, 0, (size_t)M * N, 0}, st, splits);
 }
 
+// Splitting K adds workgroups and shortens their chain, and pays for the fp32 planes: written,
+// read again and summed by a kernel of its own (about 5 us and 4.5 TB/s).
 int gemm_out_splits(int M, int N, int K) {
-    const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    const int nkt = (K + BK - 1) / BK;
-    int s = 1;
-    // One workgroup per CU: split K until the grid covers the 256 CUs (at most 8 slices, each
-    // at least one 64-wide tile).
-    while (tiles * s < 256 && 2 * s <= 8 && 2 * s <= nkt) s *= 2;
-    return s;
+    int best = 1;
+    float t = pick_tile(M, N, K, 1).us;
+    for (int s = 2; s <= 8 && s <= K / BK; s *= 2) {
+        const float u = pick_tile(M, N, K, s).us + 5.f + (float)(s + 1) * (float)M * (float)N * 4.f / 4.5e6f;
+        if (u < t) {
+            t = u;
+            best = s;
+        }
+    }
+    return best;
 }
 
 }  // namespace kvp

@@ -240,16 +240,19 @@ struct ResidEpi {
     }
 };
 
-// Plain store of C (no fused work): bf16 [M][N], or fp32 partial sums of one K slice into
-// plane `split` of out ([M][N] per plane).
+// Plain store of C (no fused work): bf16 [M][N], or fp32: rows [0, rows0) of C to dst0, the
+// next rows1 to dst1, the rest to dst2, or (split K) plane `split` of dst0.
+template <bool BF16>
 struct OutEpi {
     static constexpr bool kPairedCols = false;
     template <int ROWS, int BN, int NT>
     struct Pre {};
-    void* out;
+    void* dst0;
+    float* dst1;
+    float* dst2;
+    int rows0, rows1;
     size_t plane;
     int split;
-    bool bf16;
     __device__ __forceinline__ void set_split(int s) { split = s; }
     template <int ROWS, int BN, int NT>
     __device__ __forceinline__ void prefetch(int, int, int, int, int, Pre<ROWS, BN, NT>&) const {}
@@ -260,19 +263,28 @@ struct OutEpi {
 #pragma unroll
         for (int t = 0; t < ROWS * C8 / NT; ++t) {
             const int id = tid + NT * t, row = id / C8, c8 = id % C8;
-            const int m = m0 + row, n = n0 + 8 * c8;
+            int m = m0 + row;
+            const int n = n0 + 8 * c8;
             if (m >= M || n >= N) continue;
             const u32x4 p0 = st_chunk<BN>(st, row, 2 * c8), p1 = st_chunk<BN>(st, row, 2 * c8 + 1);
-            const size_t off = (size_t)m * N + n;
-            if (bf16) {
+            if constexpr (BF16) {
                 u32x4 o;
                 o[0] = pack2bf(__uint_as_float(p0[0]), __uint_as_float(p0[1]));
                 o[1] = pack2bf(__uint_as_float(p0[2]), __uint_as_float(p0[3]));
                 o[2] = pack2bf(__uint_as_float(p1[0]), __uint_as_float(p1[1]));
                 o[3] = pack2bf(__uint_as_float(p1[2]), __uint_as_float(p1[3]));
-                *(u32x4*)((uint16_t*)out + off) = o;
+                *(u32x4*)((uint16_t*)dst0 + (size_t)m * N + n) = o;
             } else {
-                float* dst = (float*)out + split * plane + off;
+                float* dst = (float*)dst0;
+                if (m >= rows0) {
+                    m -= rows0;
+                    dst = dst1;
+                    if (m >= rows1) {
+                        m -= rows1;
+                        dst = dst2;
+                    }
+                }
+                dst += split * plane + (size_t)m * N + n;
                 *(u32x4*)dst = p0;
                 *(u32x4*)(dst + 4) = p1;
             }

@@ -57,27 +57,36 @@ hipError_t flash_prefill_bf16(const uint16_t* q, const uint16_t* kc, const uint1
                               uint16_t* o, float* lse, uint16_t* ot, int Sp, int B, int S, int a, int g,
                               int cap, const Pages& pages, hipStream_t st);
 
-// The slice count gemm_kmajor_out_bf16 should use for an M x N x K product.
-int gemm_out_splits(int M, int N, int K);
-
-// C[M][N] = sum_k a[k][m] b[k][n] with a [K][lda], b [K][ldb] K-major (the backward's weight
-// gradients; any K; M, N, lda, ldb % 8 == 0), split over `splits` ranges of whole 64-wide K
-// tiles, fp32 partials to part + s * M * N.
-hipError_t gemm_kmajor_out_bf16(const uint16_t* a, int lda, const uint16_t* b, int ldb, int M, int N, int K,
-                                int splits, float* part, hipStream_t st);
-// C = a @ w^T in bf16 (a [M][K], w [N][K], K % 64 == 0), no fused work.
-// part[s][M][N] (fp32, s < splits) = the K slice s of a @ w^T (a [M][K], w [N][K], both
-// K-contiguous); K a multiple of 64 * splits.
-hipError_t gemm_nt_out_splits(const uint16_t* a, const uint16_t* w, int M, int N, int K, int splits, float* part,
-                              hipStream_t st);
+// c = a @ w^T in bf16 (a [M][K], w [N][K], K % 64 == 0), no fused work.
 hipError_t gemm_out_bf16(const uint16_t* a, const uint16_t* w, int M, int N, int K, uint16_t* c,
                          hipStream_t st);
+// The same in fp32 over `splits` slices of K (whole 64-wide tiles): splits == 1 writes rows
+// [0, rows0) to dst0, then rows1 to dst1, the rest to dst2; else part[s][M][N] receives
+// slice s (sum them with reduce_planes).
+hipError_t gemm_out_f32(const uint16_t* a, const uint16_t* w, int M, int N, int K, int splits, float* part, float* dst0,
+                        int rows0, float* dst1, int rows1, float* dst2, hipStream_t st);
+// The slice count gemm_out_f32 should use for an M x N x K product.
+int gemm_out_splits(int M, int N, int K);
 
 // ---- bf16 backward ----------------------------------------------------------
 
-// out[c][r] = in[r][c] for r < R, c < C (row strides in_ld, out_ld).
-hipError_t transpose_bf16(const uint16_t* in, uint16_t* out, int R, int C, size_t in_ld, size_t out_ld,
-                          hipStream_t st);
+// Up to 8 transposes in one launch: out[c][r] = in[r][c] for r < R, c < C (row strides in_ld,
+// out_ld), zeros for R <= r < R rounded up to 64.  C, in_ld, out_ld multiples of 64, buffers
+// 16-byte aligned.
+struct Transposes {
+    static constexpr int kMax = 8;
+    struct Job {
+        const uint16_t* in;
+        uint16_t* out;
+        int R, C, in_ld, out_ld;
+    } job[kMax];
+    int first[kMax + 1];    // first workgroup of each job (filled by the launch)
+    int n = 0;
+    void add(const void* in, uint16_t* out, int R, int C, int in_ld, int out_ld) {
+        job[n++] = {(const uint16_t*)in, out, R, C, in_ld, out_ld};
+    }
+};
+hipError_t transpose_bf16(Transposes t, hipStream_t st);
 hipError_t f32_to_bf16(const float* x, uint16_t* y, size_t n, hipStream_t st);
 // Sum of `planes` [M][N] fp32 planes; rows [0, rows0) -> dst0, then rows1 -> dst1, rest -> dst2.
 hipError_t reduce_planes(const float* part, int planes, int M, int N, float* dst0, int rows0, float* dst1,
@@ -102,7 +111,9 @@ struct AttnBwdKv {
     uint16_t* out_t;        // nullable: the same rows token-major, [ldo][B*S] (S % 8 == 0)
     int ldo, col_k, col_v;
     int B, S, Sp, a, g, cap;
+    float* part;            // bwd_kv_part_floats() of scratch (null when that is 0)
 };
+size_t bwd_kv_part_floats(int B, int S, int a, int g);
 hipError_t flash_bwd_kv_bf16(const AttnBwdKv& p, hipStream_t st);
 
 struct AttnBwdQ {

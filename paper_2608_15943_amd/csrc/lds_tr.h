@@ -1,5 +1,5 @@
 // LDS tiles read along their rows with the gfx950 transpose read (ds_read_b64_tr_b16),
-// shared by the backward attention kernels and the GEMM's transposed-operand paths.
+// for the backward attention kernels.
 #pragma once
 
 #include "common.h"

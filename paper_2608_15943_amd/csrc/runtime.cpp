@@ -619,11 +619,10 @@ namespace {
 
 int round64(int S) { return (S + 63) / 64 * 64; }
 
-// Token counts that are multiples of this take the row-major weight-gradient GEMMs on
-// transposed activations (64-wide K tiles times up to 8 split-K slices).
+// Token counts that are multiples of kTokGrain, with S % 8 == 0 (aligned token runs): the
+// attention kernels write O^T and [dQ|dK|dV]^T, the token-major operands of the weight
+// gradients, themselves.  Others are transposed by a kernel, padded to whole 64-token tiles.
 constexpr int kTokGrain = 512;
-// On that path, when S % 8 == 0, the attention kernels write O^T and [dQ|dK|dV]^T
-// themselves (8-byte aligned token runs) instead of separate transposes.
 bool tokmajor_direct(int B, int S) { return (size_t)B * S % kTokGrain == 0 && S % 8 == 0; }
 
 // Per-layer activations of kvp_train_forward, layer l at l * stride: Q (after RoPE), the
@@ -658,7 +657,7 @@ Saved saved_layout(const kvp_ctx& c, int B, int S) {
 // Workspace of kvp_backward.
 struct BwdWs {
     size_t gb = 0, dO = 0, lse = 0, dsum = 0, dqkv = 0, acc = 0, wot = 0, wst = 0, part = 0, rope = 0, ta = 0, tb = 0,
-           total = 0;
+           tc = 0, total = 0;
     size_t acc_plane = 0;          // floats of one dK or dV sum
     std::vector<int> acc_slot;     // per layer: index of its fp32 sum pair, or -1
 };
@@ -702,18 +701,22 @@ BwdWs bwd_layout(const kvp_ctx& c, int B, int S) {
     w.acc = take((size_t)nacc * 2 * w.acc_plane * sizeof(float));
     w.wot = take(nq * h * 2);   // W_O^T [a*d_h][h]
     w.wst = take(h * np * 2);   // [W_Q; W_K; W_V]^T [h][np]
-    // Split-K partial planes of the weight-gradient GEMMs (consumers: Q rows only).
-    const int so = kvp::gemm_out_splits((int)h, (int)nq, (int)M);
-    const int sp = kvp::gemm_out_splits((int)np, (int)h, (int)M);
-    const int sc = kvp::gemm_out_splits((int)nq, (int)h, (int)M);
-    w.part = take(std::max({(size_t)so * h * nq, (size_t)sp * np * h, (size_t)sc * nq * h}) * sizeof(float));
+    // Scratch of one step at a time: split-K planes of the weight-gradient GEMMs (consumers: Q
+    // rows only), or the chunk sums of dK, dV.
+    const size_t Mp = (M + 63) / 64 * 64;
+    auto planes = [&](size_t m, size_t n) {
+        const int sp = kvp::gemm_out_splits((int)m, (int)n, (int)Mp);
+        return sp > 1 ? sp * m * n : (size_t)0;
+    };
+    w.part = take(std::max({planes(h, nq), planes(np, h), planes(nq, h),
+                            kvp::bwd_kv_part_floats(B, S, c.d.a, c.d.g)}) *
+                  sizeof(float));
     w.rope = take((size_t)S * 64 * sizeof(float2));
-    // Token-major copies for the row-major weight-gradient GEMMs (token counts that are
-    // multiples of 512): G^T or [dQ|dK|dV]^T, and O^T or X^T.
-    if (M % kTokGrain == 0) {
-        w.ta = take(M * std::max(h, np) * 2);
-        w.tb = take(M * std::max(h, nq) * 2);
-    }
+    // Token-major operands of the weight-gradient GEMMs: G^T then [dQ|dK|dV]^T; X^T; O^T
+    // unless the forward saved it.
+    w.ta = take(Mp * std::max(h, np) * 2);
+    w.tb = take(Mp * h * 2);
+    if (!tokmajor_direct(B, S)) w.tc = take(Mp * nq * 2);
     w.total = off;
     return w;
 }
@@ -1127,6 +1130,7 @@ extern "C" int kvp_backward(kvp_ctx* ctx, const void* x, const void* dy, void* d
     if ((rc = aux([&] { return check_hip(kvp::f32_to_bf16((const float*)dy, gb, (size_t)M * h, st), "cast dY"); })))
         return rc;
 
+    const int Mp = (M + 63) / 64 * 64;   // tokens of the token-major copies, zeros past M
     std::vector<char> acc_written(L, 0);
     for (int l = L - 1; l >= 0; --l) {
         const int p = ctx->tau[l];
@@ -1140,41 +1144,44 @@ extern "C" int kvp_backward(kvp_ctx* ctx, const void* x, const void* dy, void* d
         const float* lse = (const float*)(lay + sv.lse);
         const uint16_t* Xl = l == 0 ? (const uint16_t*)x : (const uint16_t*)(lay + sv.x);
 
-        // dO = G W_O (on W_O^T), D = rowsum(dO * O), dW_O = G^T O (both K-major over the tokens).
+        // The operands known so far, in one launch: W_O^T, [W_Q; W_K; W_V]^T, G^T, X^T (, O^T).
+        uint16_t *ta = bp(w.ta), *tb = bp(w.tb), *tc = bp(w.tc);
+        const uint16_t* Ot = sv.has_ot ? (const uint16_t*)(lay + sv.ot) : tc;
         if ((rc = aux([&] {
-                 return check_hip(kvp::transpose_bf16((const uint16_t*)Ly.wo, wot, h, nq, nq, h, st), "transpose W_O");
+                 kvp::Transposes t;
+                 t.add(Ly.wo, wot, h, nq, nq, h);
+                 t.add(Ly.wq, wst, nq, h, h, np);
+                 if (producer) {
+                     t.add(Ly.wk, wst + nq, nkv, h, h, np);
+                     t.add(Ly.wv, wst + nq + nkv, nkv, h, h, np);
+                 }
+                 t.add(gb, ta, M, h, h, Mp);
+                 t.add(Xl, tb, M, h, h, Mp);
+                 if (!sv.has_ot) t.add(Ol, tc, M, nq, nq, Mp);
+                 return check_hip(kvp::transpose_bf16(t, st), "transposes");
              })))
             return rc;
+        // dO = G W_O (on W_O^T), D = rowsum(dO * O), dW_O = G^T O (over the token-major copies).
         if ((rc = gemm([&] { return check_hip(kvp::gemm_out_bf16(gb, wot, M, nq, h, dO, st), "dO GEMM"); })))
             return rc;
         if ((rc = aux([&] {
                  return check_hip(kvp::attn_bwd_prep_bf16(dO, Ol, dsum, B, S, Sp, ctx->d.a, st), "attention backward D");
              })))
             return rc;
-        const bool nt = M % kTokGrain == 0;
-        uint16_t* ta = bp(w.ta);
-        uint16_t* tb = bp(w.tb);
-        {
-            const int s = kvp::gemm_out_splits(h, nq, M);
-            if (nt) {
-                // dW_O = G^T O on the token-major copies (row-major GEMM, split K); O^T was
-                // saved by the forward's attention kernel when S % 8 == 0.
-                const uint16_t* Ot = sv.has_ot ? (const uint16_t*)(lay + sv.ot) : tb;
-                if ((rc = aux([&] {
-                         int r2 = check_hip(kvp::transpose_bf16(gb, ta, M, h, h, M, st), "transpose G");
-                         if (!r2 && !sv.has_ot) r2 = check_hip(kvp::transpose_bf16(Ol, tb, M, nq, nq, M, st), "transpose O");
-                         return r2;
-                     })))
-                    return rc;
-                if ((rc = gemm([&] { return check_hip(kvp::gemm_nt_out_splits(ta, Ot, h, nq, M, s, part, st), "dW_O GEMM"); })))
-                    return rc;
-            } else if ((rc = gemm([&] { return check_hip(kvp::gemm_kmajor_out_bf16(gb, h, Ol, nq, h, nq, M, s, part, st), "dW_O GEMM"); })))
-                return rc;
-            if ((rc = aux([&] {
-                     return check_hip(kvp::reduce_planes(part, s, h, nq, Ly.dwo, h, nullptr, 0, nullptr, st), "dW_O sum");
-                 })))
-                return rc;
-        }
+        // C = a^T b over the tokens, rows to up to three gradient buffers.
+        auto weight_grad = [&](const uint16_t* at, const uint16_t* bt, int rows, int cols, float* d0, int r0, float* d1,
+                               int r1, float* d2, const char* what) {
+            const int s = kvp::gemm_out_splits(rows, cols, Mp);
+            int r2 = gemm([&] {
+                return check_hip(kvp::gemm_out_f32(at, bt, rows, cols, Mp, s, part, d0, r0, d1, r1, d2, st), what);
+            });
+            if (!r2 && s > 1)
+                r2 = aux([&] {
+                    return check_hip(kvp::reduce_planes(part, s, rows, cols, d0, r0, d1, r1, d2, st), what);
+                });
+            return r2;
+        };
+        if ((rc = weight_grad(ta, Ot, h, nq, Ly.dwo, h, nullptr, 0, nullptr, "dW_O"))) return rc;
         // dK, dV: a consumer adds into its producer's fp32 sums; the producer finishes them.
         {
             kvp::AttnBwdKv a{};
@@ -1199,6 +1206,7 @@ extern "C" int kvp_backward(kvp_ctx* ctx, const void* x, const void* dy, void* d
                 a.col_v = nq + nkv;
             }
             a.B = B; a.S = S; a.Sp = Sp; a.a = ctx->d.a; a.g = ctx->d.g; a.cap = ctx->d.kv_capacity;
+            a.part = part;
             if ((rc = timed(ctx, KVP_K_BWD_ATTN_KV, st, [&] {
                      return check_hip(kvp::flash_bwd_kv_bf16(a, st), "attention backward dK dV");
                  })))
@@ -1215,44 +1223,16 @@ extern "C" int kvp_backward(kvp_ctx* ctx, const void* x, const void* dy, void* d
                  })))
                 return rc;
         }
-        // dW_Q (| dW_K | dW_V) = [dQ | dK | dV]^T X_l (both K-major over the tokens).
-        {
-            const int s = kvp::gemm_out_splits(np, h, M);
-            if (nt) {
-                if ((rc = aux([&] {
-                         int r2 = sv.has_ot ? 0 : check_hip(kvp::transpose_bf16(dqkv, ta, M, np, np, M, st),
-                                                            "transpose dQKV");
-                         if (!r2) r2 = check_hip(kvp::transpose_bf16(Xl, tb, M, h, h, M, st), "transpose X");
-                         return r2;
-                     })))
-                    return rc;
-                if ((rc = gemm([&] { return check_hip(kvp::gemm_nt_out_splits(ta, tb, np, h, M, s, part, st), "dW_QKV GEMM"); })))
-                    return rc;
-            } else if ((rc = gemm([&] {
-                            return check_hip(kvp::gemm_kmajor_out_bf16(dqkv, np, Xl, h, np, h, M, s, part, st),
-                                             "dW_QKV GEMM");
-                        })))
-                return rc;
-            if ((rc = aux([&] {
-                     return check_hip(kvp::reduce_planes(part, s, np, h, Ly.dwq, nq, Ly.dwk, producer ? nkv : 0,
-                                                         Ly.dwv, st),
-                                      "dW_QKV sum");
-                 })))
-                return rc;
-        }
-        // dX_l = dX_{l+1} + [dQ | dK | dV] [W_Q; W_K; W_V] (on the stacked weights transposed
-        // to [h][np]).
-        if ((rc = aux([&] {
-                 int r2 = check_hip(kvp::transpose_bf16((const uint16_t*)Ly.wq, wst, nq, h, h, np, st), "transpose W_Q");
-                 if (!r2 && producer)
-                     r2 = check_hip(kvp::transpose_bf16((const uint16_t*)Ly.wk, wst + nq, nkv, h, h, np, st),
-                                    "transpose W_K");
-                 if (!r2 && producer)
-                     r2 = check_hip(kvp::transpose_bf16((const uint16_t*)Ly.wv, wst + nq + nkv, nkv, h, h, np, st),
-                                    "transpose W_V");
-                 return r2;
+        // dW_Q (| dW_K | dW_V) = [dQ | dK | dV]^T X_l.
+        if (!sv.has_ot && (rc = aux([&] {
+                 kvp::Transposes t;
+                 t.add(dqkv, ta, M, np, np, Mp);
+                 return check_hip(kvp::transpose_bf16(t, st), "transpose dQKV");
              })))
             return rc;
+        if ((rc = weight_grad(ta, tb, np, h, Ly.dwq, nq, Ly.dwk, producer ? nkv : 0, Ly.dwv, "dW_QKV"))) return rc;
+        // dX_l = dX_{l+1} + [dQ | dK | dV] [W_Q; W_K; W_V] (on the stacked weights transposed to
+        // [h][np]).
         {
             const void* gres = l == L - 1 ? dy : dx;
             if ((rc = gemm([&] {

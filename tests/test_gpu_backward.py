@@ -121,6 +121,12 @@ def _train_case(w, B, S, cap):
     # an 8-token tail (40), take the partial-run stores.
     (256, 2, 1, [0, 0], 64, 8),
     (256, 2, 1, [0, 0, 2], 64, 40),
+    # dK, dV of few key blocks: their query blocks dealt to several workgroups and summed; a
+    # key count past a block and past a 32-key run (row-major and token-major outputs), and
+    # token counts that leave the last 64-token tile of the weight gradients part zeros.
+    (512, 4, 1, [0, 0], 2, 531),
+    (256, 2, 2, [0, 1], 1, 1090),
+    (512, 4, 1, [0, 0, 0], 1, 512),
 ])
 def test_backward_matches_oracle(h, a, g, tau, B, S):
     w = small_workload(f"bwd-h{h}-a{a}-g{g}", len(tau), h, a, g, tau, seed=21)
