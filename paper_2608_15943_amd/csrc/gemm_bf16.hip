@@ -16,8 +16,8 @@
 // has two slots pairs (a whole K step of the workgroup) before its wait, which leaves the
 // newer loads in flight.
 //
-// gemm_small: BM x BN (128 x 128, 64 x 64) per workgroup of 4 waves, several workgroups per
-// CU, a ring of LDS stages: products whose 256 x 256 tiles would leave CUs without work.
+// gemm_half (128 x 256, the same turns) and gemm_small (128 x 128, 64 x 64 per workgroup of 4
+// waves): products whose 256 x 256 tiles would leave CUs without work.
 //
 // LDS rows are 128 B (64 k) with the 16-byte chunk index XOR-swizzled by ((row >> 1) & 7),
 // which spreads the fragment reads over all 64 banks.  Tiles are ordered so that each XCD
@@ -289,11 +289,112 @@ __global__ __launch_bounds__(kBigNT, 2) void gemm_big(const uint16_t* __restrict
     }
 }
 
+// 128 x 256 tile, the first of gemm_big's two phases alone: 64 x 64 per wave, 16 products a
+// slot.  A K tile is one read slot and one product slot per group; three stages of 48 KB, tile
+// kt + 3 requested in the read slot of tile kt + 1 (both groups have read tile kt by then) and
+// waited for in that of tile kt + 2.
+template <class Epi>
+__global__ __launch_bounds__(kBigNT, 2) void gemm_half(const uint16_t* __restrict__ A, WRows W, int M, int N, int K,
+                                                      int splits, Epi epi) {
+    constexpr int kStage = 384 * 8;            // [A 128 rows, B 256 rows][8 chunks]
+    __shared__ u32x4 lds[3 * kStage];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const int l32 = lane & 31, hi = lane >> 5;
+
+    const int ntm = (M + 127) / 128, ntn = (N + BN - 1) / BN;
+    const int lid0 = xcd_remap(blockIdx.x, gridDim.x);
+    const int split = __builtin_amdgcn_readfirstlane(lid0 / (ntm * ntn));
+    int tm, tn;
+    tile_of(lid0 - split * (ntm * ntn), ntm, ntn, 2 * GROUP_M, tm, tn);
+    const int m0 = tm * 128, n0 = tn * BN;
+    const int kt0 = __builtin_amdgcn_readfirstlane(split * (K / BK) / splits);
+    const int nk = __builtin_amdgcn_readfirstlane((split + 1) * (K / BK) / splits) - kt0, kofs = kt0 * BK;
+    epi.set_split(split);
+
+    const __amdgpu_buffer_rsrc_t ra = row_rsrc(A + (size_t)m0 * K, min(M - m0, 128), K);
+    const __amdgpu_buffer_rsrc_t rb[2] = {row_rsrc(w_block(W, n0, K), 128, K),
+                                          row_rsrc(w_block(W, n0 + 128 < N ? n0 + 128 : n0, K), 128, K)};
+    uint32_t goff[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int row = 16 * wave + 8 * j + (lane >> 3);
+        goff[j] = (uint32_t)(row * K + kofs + 8 * swz(row, lane & 7)) * 2u;
+    }
+    auto issue = [&](int kt, int stg) __attribute__((always_inline)) {
+        u32x4* dst = &lds[stg * kStage + wave * 128];
+        const uint32_t past = kt < nk ? 0u : 0x80000000u;
+        const int ko = kt < nk ? kt * BK * 2 : 0;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            load_1k(ra, dst + 64 * j, goff[j] | past, ko);
+            load_1k(rb[0], dst + 1024 + 64 * j, goff[j] | past, ko);
+            load_1k(rb[1], dst + 2048 + 64 * j, goff[j] | past, ko);
+        }
+    };
+    f32x16 c[2][2];   // [column half][32-row block]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[i >> 1][i & 1] = f32x16{};
+    Frag fa[2], fb[2];
+
+    issue(0, 0);
+    issue(1, 1);
+    issue(2, 2);
+    vm_wait<12>();
+    slot_end();
+    if (wm == 1) slot_end();   // the second group runs one slot behind
+    int stg = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        if (kt > 0) issue(kt + 2, stg == 0 ? 2 : stg - 1);
+        uint32_t aa[4], ab[4];
+        const uint32_t base = (uint32_t)(uintptr_t)&lds[0] + stg * (kStage * 16);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const uint32_t ch = (uint32_t)(((2 * ks + hi) ^ ((l32 >> 1) & 7)) * 16);
+            aa[ks] = base + (64 * wm + l32) * 128 + ch;
+            ab[ks] = base + 16384 + (32 * wn + l32) * 128 + ch;
+        }
+        read_a2b2_half(fa, fb, aa, ab);
+        vm_wait<6>();
+        slot_end();
+        asm volatile("" : "+v"(c[0][0]), "+v"(c[0][1]), "+v"(c[1][0]), "+v"(c[1][1]));
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+                    c[j][mb] = mfma32x32x16(as_bf16x8(fa[mb][ks]), as_bf16x8(fb[j][ks]), c[j][mb]);
+        __builtin_amdgcn_s_setprio(0);
+        asm volatile("" : "+v"(c[0][0]), "+v"(c[0][1]), "+v"(c[1][0]), "+v"(c[1][1]));
+        slot_end();
+        stg = stg == 2 ? 0 : stg + 1;
+    }
+    if (wm == 0) slot_end();
+    vm_wait<0>();
+    char* st = (char*)&lds[0];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) st_block<BN>(st, c[j][mb], 64 * wm + 32 * mb, 128 * j + 32 * wn, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    typename Epi::template Pre<128, BN, kBigNT> pre;
+    epi.template prefetch<128, BN, kBigNT>(m0, n0, tid, M, N, pre);
+    __syncthreads();
+    epi.template flush<128, BN, kBigNT>(m0, n0, tid, M, N, st, pre);
+}
+
 // BM_ x BN_ tile of 4 waves (2 x 2), STAGES K tiles in LDS: tile kt + STAGES - 1 is requested
 // once tile kt - 1 is read, and a wave waits only for tile kt's loads, so STAGES - 1 tiles of
-// latency are covered; other workgroups of the CU run under the rest.
-template <class Epi, int BM_, int BN_, int STAGES, int GM>
-__global__ __launch_bounds__(256, 2) void gemm_small(const uint16_t* __restrict__ A, WRows W, int M, int N, int K,
+// latency are covered; another workgroup of the CU (PER_CU = 2) runs under the rest.  Stages
+// and K per stage measured: 128 x 128 tiles, one round of 256 (1024 tokens at width 4096,
+// output): 2 stages 63 us, 3 stages 46.5, 4 stages 47; 64 x 64 (200 tokens, width 4096): 4
+// stages 33 us, 5 stages 33, 8 stages 41 (one workgroup per CU), 128 of K per stage 34 to 40.
+template <class Epi, int BM_, int BN_, int STAGES, int GM, int PER_CU>
+__global__ __launch_bounds__(256, PER_CU) void gemm_small(const uint16_t* __restrict__ A, WRows W, int M, int N, int K,
                                                     int splits, Epi epi) {
     constexpr int ROWS = BM_ + BN_, LPT = ROWS / 32;   // LDS rows of a stage, loads per wave and tile
     constexpr int MB = BM_ / 64, NB = BN_ / 64;
@@ -394,27 +495,32 @@ __global__ __launch_bounds__(256, 2) void gemm_small(const uint16_t* __restrict_
 }
 
 // Estimated time (us) of a product on each tile, k = K / 1024, t = number of tiles: fitted to
-// the layer projections at widths 2048, 4096 and 8192 and 64 to 16384 tokens.  A 256 x 256
-// tile has a CU to itself; a round costs 13 + 13.5 k with few CUs busy and 17.5 + 21.7 k with
-// all of them (the matrix cores' clock falls, the epilogues share the HBM).  The small tiles
-// run two workgroups per CU: a floor for one wave of workgroups, then 512 at a time.
-// Measured (us, 256 / 128 / 64): 200 tokens at width 4096, Q|K|V 73 / 44 / 26; 1024 tokens
-// at 2048, output 40 / 25 / 18; 3000 tokens at 2048, Q|K|V 55 / 59 / 81, output 42 / 33 / 43;
-// 8192 tokens at 8192, Q|K|V 978 / 1217 / 2407.
+// the layer projections at widths 2048, 4096 and 8192 and 64 to 16384 tokens with weights read
+// from HBM.  The 256 x 256, 128 x 256 and 128 x 128 tiles have a CU to themselves: a round
+// takes longer with every CU busy than with few (the matrix cores' clock falls, the epilogues
+// share the HBM).  The 64 x 64 tiles run two workgroups per CU.  Measured (us; big / half /
+// 128 / 64): 200 tokens at width 4096, Q|K|V 79 / 56 / 44 / 33; 1024 tokens at 2048, output
+// 42 / 33 / 26 / 21; 1024 tokens at 4096, Q|K|V 84 / 62 / 88 / 97; 3000 tokens at 2048, output
+// 43 / 34 / 47 / 49, Q|K|V 56 / 67 / 72 / 91; 8192 tokens at 8192, output 757 / 963 / - / -.
+enum Tile { kBig, kHalf, kMid, kLow };
 struct Pick {
-    int tile;
+    Tile tile;
     float us;
 };
+int64_t tiles(int M, int N, int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 Pick pick_tile(int M, int N, int K, int splits) {
     const float k = (float)K / (float)splits / 1024.f;
-    auto tiles = [&](int b) { return (int64_t)((M + b - 1) / b) * ((N + b - 1) / b) * splits; };
-    const int64_t t = tiles(256), rest = t % 256;
-    float big = (float)(t / 256) * (17.5f + 21.7f * k);
-    if (rest) big += 13.f + 13.5f * k + (float)rest / 256.f * (4.5f + 8.2f * k);
-    const float mid = std::max(7.f + 8.8f * k, (float)tiles(128) / 512.f * (9.f + 13.4f * k));
-    const float low = std::max(6.5f + 3.5f * k, (float)tiles(64) / 512.f * (8.f + 5.1f * k));
-    if (low < mid && low < big) return {64, low};
-    return mid < big ? Pick{128, mid} : Pick{256, big};
+    auto rounds = [&](int64_t t, float full, float least, float load) {
+        return (float)(t / 256) * full + (t % 256 ? least + (float)(t % 256) / 256.f * load : 0.f);
+    };
+    Pick p{kBig, rounds(tiles(M, N, 256, 256) * splits, 17.5f + 21.7f * k, 13.f + 13.5f * k, 4.5f + 8.2f * k)};
+    const float half = rounds(tiles(M, N, 128, 256) * splits, 10.5f + 13.4f * k, 3.f + 13.3f * k, 7.f);
+    if (half < p.us) p = {kHalf, half};
+    const float mid = rounds(tiles(M, N, 128, 128) * splits, 10.f + 9.5f * k, 5.5f + 9.5f * k, 2.5f);
+    if (mid < p.us) p = {kMid, mid};
+    const float low = std::max(2.f + 5.5f * k, (float)(tiles(M, N, 64, 64) * splits) / 512.f * (3.f + 7.5f * k));
+    if (low < p.us) p = {kLow, low};
+    return p;
 }
 
 template <class Epi>
@@ -422,14 +528,24 @@ hipError_t launch(const uint16_t* A, const WRows& W, int M, int N, int K, const 
                   hipStream_t st, int splits = 1) {
     if (M < 1 || N % 128 || K % BK || splits < 1 || splits > K / BK)
         return hipErrorInvalidValue;
-    const int b = pick_tile(M, N, K, splits).tile;
-    const dim3 grid(((M + b - 1) / b) * ((N + b - 1) / b) * splits);
-    if (b == 64)
-        hipLaunchKernelGGL((gemm_small<Epi, 64, 64, 4, 16>), grid, dim3(256), 0, st, A, W, M, N, K, splits, epi);
-    else if (b == 128)
-        hipLaunchKernelGGL((gemm_small<Epi, 128, 128, 2, 8>), grid, dim3(256), 0, st, A, W, M, N, K, splits, epi);
-    else
-        hipLaunchKernelGGL(gemm_big<Epi>, grid, dim3(kBigNT), 0, st, A, W, M, N, K, splits, epi);
+    switch (pick_tile(M, N, K, splits).tile) {
+        case kBig:
+            hipLaunchKernelGGL(gemm_big<Epi>, dim3(tiles(M, N, 256, 256) * splits), dim3(kBigNT), 0, st, A, W, M, N, K,
+                               splits, epi);
+            break;
+        case kHalf:
+            hipLaunchKernelGGL(gemm_half<Epi>, dim3(tiles(M, N, 128, 256) * splits), dim3(kBigNT), 0, st, A, W, M, N, K,
+                               splits, epi);
+            break;
+        case kMid:
+            hipLaunchKernelGGL((gemm_small<Epi, 128, 128, 3, 8, 1>), dim3(tiles(M, N, 128, 128) * splits), dim3(256), 0,
+                               st, A, W, M, N, K, splits, epi);
+            break;
+        case kLow:
+            hipLaunchKernelGGL((gemm_small<Epi, 64, 64, 4, 16, 2>), dim3(tiles(M, N, 64, 64) * splits), dim3(256), 0, st,
+                               A, W, M, N, K, splits, epi);
+            break;
+    }
     return hipGetLastError();
 }
 

@@ -99,7 +99,6 @@ struct QkvEpi {
             if (reg == 2) {
                 // V^T: item (column n, positions 8 k .. 8 k + 7), consecutive lanes along k.
                 constexpr int KC = ROWS / 8, TV = KC * 2 * HALF / NT;
-                const bool fast = (o.S % 8) == 0;
 #pragma unroll
                 for (int t = 0; t < TV; ++t) {
                     const int id = tid + NT * t;
@@ -112,9 +111,11 @@ struct QkvEpi {
                     const u32x4 v = {pack2bf(x[0], x[1]), pack2bf(x[2], x[3]), pack2bf(x[4], x[5]), pack2bf(x[6], x[7])};
                     const int dim = BN == 64 ? sub + (n & 31) + 2 * (n & 32) : n;
                     const int b = m / o.S, s = m - b * o.S;
-                    if (fast && m + 7 < M) {
-                        // s % 8 == 0: the 8 positions never straddle a 64-position page.
-                        *(u32x4*)(o.vc + v_at(b, head, dim, s)) = v;
+                    if (s + 8 <= o.S && m + 8 <= M && (!o.pages.pt || s % kPage <= kPage - 8)) {
+                        // One run of 8 positions of a sequence (and of a page): a 16-byte store
+                        // even where s is odd (global memory takes any alignment; eight 2-byte
+                        // stores made the epilogue 10 us longer at S = 777).
+                        __builtin_memcpy(o.vc + v_at(b, head, dim, s), &v, 16);
                     } else {
                         for (int e = 0; e < 8 && m + e < M; ++e) {
                             int bb = b, ss = s + e;

@@ -42,7 +42,9 @@ def _forward(dm, B, S):
     (3, 1, 1, 65),
     (3, 3, 3, 43),       # 129 rows, positions not a multiple of 8
     (3, 1, 40, 67),
-    (3, 1, 300, 67),     # 20100 rows: 128-wide tiles, 4 rows in the last
+    (3, 1, 300, 67),     # 20100 rows: 256-wide tiles, 132 rows in the last, half of a column tile
+    (16, 8, 12, 127),    # 1524 rows at width 2048: 128 x 256 tiles, then 128 x 128
+    (33, 3, 9, 127),     # 1143 rows at width 4224: 128 x 256 tiles, the last column tile half empty
     (16, 8, 33, 127),    # 4191 rows at width 2048: 256-wide tiles, 95 rows in the last
     (33, 3, 245, 67),    # 16415 rows at width 4224: 256-wide tiles, the last column tile half empty
 ])
