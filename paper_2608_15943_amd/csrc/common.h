@@ -73,14 +73,28 @@ __device__ __forceinline__ float pair16_sum(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Value of another lane of the row of 16 (a DPP modifier: no LDS traffic; a bpermute shuffle
+// is some 100 cycles, and a reduction six of them one after the other).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), CTRL, 0xF, 0xF, true));
+}
+// Lanes i ^ 1, i ^ 2, then 7 - i of 8 and 15 - i of 16 (whose quads and eights are uniform by
+// then), then the other rows.
 __device__ __forceinline__ float wave_max(float v) {
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    v = fmaxf(v, dpp<0xB1>(v));
+    v = fmaxf(v, dpp<0x4E>(v));
+    v = fmaxf(v, dpp<0x141>(v));
+    v = fmaxf(v, dpp<0x140>(v));
+    return pair32_max(pair16_max(v));
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    v += dpp<0xB1>(v);
+    v += dpp<0x4E>(v);
+    v += dpp<0x141>(v);
+    v += dpp<0x140>(v);
+    return pair32_sum(pair16_sum(v));
 }
 
 }  // namespace kvp

@@ -4,10 +4,12 @@
 //
 // Schedule: the work of one layer is the list of 64-position tiles of every
 // (sequence b, KV head) pair, in (b, head, tile) order.  The grid has one wave per
-// SIMD of the device, all resident at once, and wave w streams the contiguous
-// range [w c, (w + 1) c) of that list with c = ceil(tiles / waves): every wave
-// reads the same number of bytes whatever the mix of lengths, and a range may run
-// from the end of one pair into the next without a pipeline bubble.  Each piece
+// SIMD of the device, all resident at once, and wave w streams a contiguous
+// range of that list: every wave reads the same number of tiles, or one more (the
+// T mod W of the waves), whatever the mix of lengths, and a range may run
+// from the end of one pair into the next without a pipeline bubble.  (With ranges of
+// ceil(T / W) tiles the last waves had none: 8 sequences of 4100 positions are 4.004
+// tiles a wave, 5 for four fifths of the waves, 26.7 us.)  Each piece
 // of a range that lies in one pair ends in a partial result (running max m, sum
 // l, unnormalised O); the piece of wave w in pair P goes to slot w + P, which is
 // unique because w and P never both decrease along the list.
@@ -49,13 +51,27 @@ __device__ __forceinline__ SeqTiles seq_tiles(const int32_t* lens, int B, int ca
     t.len = lane < B ? max(0, min(lens[lane], cap - 1)) + 1 : 0;
     t.n = (t.len + TILE - 1) / TILE;
     t.pre = t.n;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
+    for (int off = 1; off < B; off <<= 1) {
         const int v = __shfl_up(t.pre, off);
         if (lane >= off) t.pre += v;
     }
     return t;
 }
+
+// The list's split over W = min(waves, T) waves: wave w starts at tile floor(w T / W)
+// (T < 2^31: 64 sequences of at most 2^17 tiles and at most 256 KV heads).  Waves with one
+// tile more than others are spread over the grid: starts at one power-of-two stride (64
+// sequences of 32K: 256 tiles) meet in the same memory channels, 0.7 % slower.
+struct Split {
+    uint32_t T, W, q, rem;
+    __device__ __forceinline__ Split(uint32_t T_, uint32_t waves) : T(T_), W(min(waves, T_)), q(T_ / W), rem(T_ % W) {}
+    __device__ __forceinline__ uint32_t start(uint32_t w) const { return w * q + w * rem / W; }   // w <= W <= 4096
+    // The wave that holds tile x: ceil((x + 1) W / T) - 1.  The quotient is exact in double (an
+    // integer below 2^43 over one below 2^31).
+    __device__ __forceinline__ uint32_t wave_of(uint32_t x) const {
+        return (uint32_t)(((double)(x + 1) * (double)W - 1.0) / (double)T);
+    }
+};
 
 // One wave per workgroup, one workgroup per SIMD (the grid is sized to the device).
 // PAGED: every 64-position tile is one page, looked up once per tile.
@@ -68,17 +84,17 @@ __global__ __launch_bounds__(64, 1) void decode_attn_kernel(
     const int W = gridDim.x, w = blockIdx.x;
     const int r = a / g;
     const SeqTiles st = seq_tiles(lens, B, cap, lane);
-    const long long T = (long long)g * __shfl(st.pre, 63);
-    const long long c = (T + W - 1) / W;
-    long long x = (long long)w * c;
-    const long long x_end = min(x + c, T);
-    if (x >= x_end) return;
+    const uint32_t T = (uint32_t)g * __shfl(st.pre, B - 1);
+    const Split sp(T, W);
+    if (w >= (int)sp.W) return;
+    uint32_t x = sp.start(w);
+    const uint32_t x_end = sp.start(w + 1);
 
     // Locate tile x: sequence b is the number of sequences that end at or before x.
-    int b = __popcll(__ballot((long long)g * st.pre <= x));
+    int b = __popcll(__ballot(lane < B && (uint32_t)g * st.pre <= x));
     int n = __shfl(st.n, b), len = __shfl(st.len, b);
-    const long long rem = x - (long long)g * (__shfl(st.pre, b) - n);
-    int kvh = (int)(rem / n), t = (int)(rem % n);
+    const uint32_t into = x - (uint32_t)g * (__shfl(st.pre, b) - n);
+    int kvh = (int)(into / n), t = (int)(into % n);
 
     const int col = lane & 15, grp = lane >> 4;    // MFMA column (head) and lane group
 
@@ -270,53 +286,67 @@ __global__ __launch_bounds__(64, 1) void decode_attn_kernel(
 
 // Merge the pieces of one (sequence, query head): the waves that covered its pair are
 // w_first..w_last (recomputed from the lengths exactly as the attention kernel splits
-// the tile list).  Weights 2^(m_s - M) go to LDS, then each half of the block sums
-// every other piece for its 128 dimensions (coalesced 512-byte rows, independent
-// loads), so the merge costs a few load latencies rather than one per piece.
+// the tile list).  Wave v of the workgroup takes pieces v, v + 4, ...: lane i holds the
+// maximum and sum of its i-th, every lane two of the 128 dimensions, so nothing is shared
+// before the four waves' results meet in LDS.  The kernel is a few dependent load latencies
+// and the fetch of its own code; weights in LDS for the whole workgroup, with three barriers,
+// or the values requested early by unrolled code were 0.8 us longer at one sequence of 977
+// positions (4.4 and 5.2 us).
 __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
     const float* __restrict__ part, const int32_t* __restrict__ lens, uint16_t* __restrict__ O, int B,
     int a, int g, int cap, int W) {
-    __shared__ float wsh[kMaxDecodeSplits];
-    __shared__ float red[2][kCombineThreads / 64];
-    __shared__ float half1[D];
+    constexpr int NW = kCombineThreads / 64;
+    __shared__ float num_s[NW][D], m_s[NW], den_s[NW];
     const int bh = blockIdx.x, b = bh / a, j = bh % a, t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int r = a / g, kvh = j / r, jr = j % r;
     const SeqTiles st = seq_tiles(lens, B, cap, lane);
-    const long long T = (long long)g * __shfl(st.pre, 63);
-    const long long c = (T + W - 1) / W;
+    const Split sp((uint32_t)g * __shfl(st.pre, B - 1), W);
     const int n = __shfl(st.n, b);
-    const long long g0 = (long long)g * (__shfl(st.pre, b) - n) + (long long)kvh * n;
-    const int w_first = (int)(g0 / c), w_last = (int)((g0 + n - 1) / c);
-    const int ns = w_last - w_first + 1;
-    const float* pr = part + (((size_t)w_first + (size_t)b * g + kvh) * r + jr) * PSTRIDE;
-    const size_t step = (size_t)r * PSTRIDE;     // next wave's slot for the same pair
-    float M = -INFINITY;
-    for (int s = t; s < ns; s += kCombineThreads) M = fmaxf(M, pr[s * step + D]);
-    M = wave_max(M);
-    if (lane == 0) red[0][wave] = M;
-    __syncthreads();
-    M = red[0][0];
-#pragma unroll
-    for (int v = 1; v < kCombineThreads / 64; ++v) M = fmaxf(M, red[0][v]);
-    float den = 0.f;
-    for (int s = t; s < ns; s += kCombineThreads) {
-        const float wt = exp2f(pr[s * step + D] - M);
-        wsh[s] = wt;
-        den += wt * pr[s * step + D + 1];
+    const uint32_t g0 = (uint32_t)g * (__shfl(st.pre, b) - n) + (uint32_t)kvh * n;
+    const int w_first = __builtin_amdgcn_readfirstlane((int)sp.wave_of(g0));
+    const int ns = __builtin_amdgcn_readfirstlane((int)sp.wave_of(g0 + n - 1)) - w_first + 1;
+    const size_t step = (size_t)NW * r * PSTRIDE;     // from one of the wave's pieces to the next
+    const float* pr = part + (((size_t)w_first + (size_t)b * g + kvh + wave) * r + jr) * PSTRIDE;
+    const int mine = (ns - wave + NW - 1) / NW;
+    float M = -INFINITY, den = 0.f;
+    f32x2 num = {0.f, 0.f};
+    for (int s0 = 0; s0 < mine; s0 += 64, pr += 64 * step) {
+        const int c = min(mine - s0, 64);
+        float m = -INFINITY, l = 0.f;
+        if (lane < c) {
+            m = pr[lane * step + D];
+            l = pr[lane * step + D + 1];
+        }
+        const float Mn = fmaxf(M, wave_max(m)), f = exp2f(M - Mn);
+        const float wt = exp2f(m - Mn);
+        den = den * f + wave_sum(wt * l);
+        num *= f;
+        M = Mn;
+        for (int s = 0; s < c; ++s) {
+            const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wt), s));
+            const f32x2 x = *(const f32x2*)(pr + s * step + 2 * lane);
+            num[0] += w * x[0];
+            num[1] += w * x[1];
+        }
     }
-    den = wave_sum(den);
-    if (lane == 0) red[1][wave] = den;
+    *(f32x2*)&num_s[wave][2 * lane] = num;
+    if (lane == 0) {
+        m_s[wave] = M;
+        den_s[wave] = den;
+    }
     __syncthreads();
-    den = 0.f;
+    if (t >= D) return;
+    float Mx = m_s[0];
 #pragma unroll
-    for (int v = 0; v < kCombineThreads / 64; ++v) den += red[1][v];
-    const int d = t & (D - 1), hf = t / D;
-    float num = 0.f;
-#pragma unroll 8
-    for (int s = hf; s < ns; s += 2) num += wsh[s] * pr[s * step + d];
-    if (hf == 1) half1[d] = num;
-    __syncthreads();
-    if (hf == 0) O[(size_t)bh * D + d] = f2bf((num + half1[d]) / den);
+    for (int v = 1; v < NW; ++v) Mx = fmaxf(Mx, m_s[v]);
+    float nsum = 0.f, dsum = 0.f;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+        const float f = exp2f(m_s[v] - Mx);
+        nsum += f * num_s[v][t];
+        dsum += f * den_s[v];
+    }
+    O[(size_t)bh * D + t] = f2bf(nsum / dsum);
 }
 
 }  // namespace

@@ -190,6 +190,23 @@ __global__ __launch_bounds__(256) void decode_qkv_epi_kernel(const float* __rest
         vld = cap;
         row = pos;
     }
+    const int heads = a + (producer ? g : 0);
+    const int npairs = heads * HALF, nv = producer ? g * D : 0;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t plane = (size_t)B * N;
+    const float* pr = part + (size_t)b * N;
+    // The item's columns (c0 and, of a rotary pair, c0 + 64).  Their first kAhead slices are
+    // requested before the cos / sin of the workgroup's position are computed.
+    const bool pair = j < npairs, real = j < npairs + nv;
+    const int c0 = pair ? j / HALF * D + j % HALF : (real ? a * D + g * D + j - npairs : 0), c1 = pair ? c0 + HALF : c0;
+    constexpr int kAhead = 8;
+    float ahead[2][kAhead];
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) {
+        const size_t o = min(s, nsplit - 1) * plane;
+        ahead[0][s] = pr[o + c0];
+        ahead[1][s] = pr[o + c1];
+    }
     if (threadIdx.x < HALF) {
         const double theta = pow(base, -2.0 * threadIdx.x / D);
         double sd, cd;
@@ -197,22 +214,19 @@ __global__ __launch_bounds__(256) void decode_qkv_epi_kernel(const float* __rest
         cs[threadIdx.x] = make_float2((float)cd, (float)sd);
     }
     __syncthreads();
-    const int heads = a + (producer ? g : 0);
-    const int npairs = heads * HALF, nv = producer ? g * D : 0;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= npairs + nv) return;
-    const size_t plane = (size_t)B * N;
-    const float* pr = part + (size_t)b * N;
-    auto val = [&](int c) {
-        float v = pr[c];
-#pragma unroll 8
-        for (int s = 1; s < nsplit; ++s) v += pr[s * plane + c];
+    if (!real) return;
+    auto val = [&](int z, int c) {
+        float v = ahead[z][0];
+#pragma unroll
+        for (int s = 1; s < kAhead; ++s)
+            if (s < nsplit) v += ahead[z][s];
+        for (int s = kAhead; s < nsplit; ++s) v += pr[s * plane + c];
         return v;
     };
-    if (j < npairs) {
+    if (pair) {
         const int h = j / HALF, i = j - h * HALF;
         const float c = cs[i].x, sn = cs[i].y;
-        const float x1 = val(h * D + i), x2 = val(h * D + i + HALF);
+        const float x1 = val(0, c0), x2 = val(1, c1);
         const float o1 = x1 * c - x2 * sn, o2 = x2 * c + x1 * sn;
         if (h < a) {
             q[(size_t)b * a * D + h * D + i] = f2bf(o1);
@@ -224,7 +238,7 @@ __global__ __launch_bounds__(256) void decode_qkv_epi_kernel(const float* __rest
         }
     } else {
         const int e = j - npairs, h = e / D, c = e - h * D;
-        vc[(kv0 + (size_t)h * hstride) * D + (size_t)c * vld + row] = f2bf(val(a * D + g * D + e));
+        vc[(kv0 + (size_t)h * hstride) * D + (size_t)c * vld + row] = f2bf(val(0, c0));
     }
 }
 
@@ -264,32 +278,51 @@ __device__ __forceinline__ const uint16_t* w_row3(const WRows& w, int n, int K) 
     return (const uint16_t*)w.p[2] + (size_t)n * K;
 }
 
+// MODE 0, with at most one workgroup per CU and fewer than 16 slices: one wave more than K has
+// slices computes the workgroup's cos / sin in double while the others wait for their weights
+// (4096 columns of K = 4096, one row: 8.9 -> 8.0 us).  A CU with several workgroups hides them
+// anyway, and the larger workgroup costs it more (6144 columns, 8 rows: +0.5 us).  Between the
+// waves' own loads and products they spilled the loads (14 -> 36 us).
 template <int MODE>   // 0: projections with RoPE + cache append, 1: output projection + residual
 __global__ __launch_bounds__(1024) void gemm_decode_fused_kernel(const uint16_t* __restrict__ X, WRows W, int M,
                                                                  int N, int K, FusedQkv fq, FusedResid fr) {
     constexpr int D = 128, HALF = 64;
     __shared__ float red[16][16 * 16];   // [wave][row * 16 + column]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    __shared__ float2 cs_s[MODE == 0 ? 16 * 8 : 1];   // [row][rotary pair of the workgroup]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = K / 512;
     const int col = lane & 15, kg = lane >> 4;
     const int j = blockIdx.x;
     const int nrot = MODE == 0 ? (fq.a + (fq.producer ? fq.g : 0)) * D : 0;   // rotary columns
     const bool rot = 16 * j < nrot;
-    const int n = rot ? (j >> 3) * D + (col < 8 ? 0 : HALF) + (j & 7) * 8 + (col & 7) : 16 * j + col;
-    const int k0 = 512 * wave;
-    const uint16_t* wr = w_row3(W, n, K) + k0 + 8 * kg;
-    const uint16_t* xr = X + (size_t)min(col, M - 1) * K + k0 + 8 * kg;
-    u32x4 wf[16], xf[16];
+    if (wave < nw) {
+        const int n = rot ? (j >> 3) * D + (col < 8 ? 0 : HALF) + (j & 7) * 8 + (col & 7) : 16 * j + col;
+        const int k0 = 512 * wave;
+        const uint16_t* wr = w_row3(W, n, K) + k0 + 8 * kg;
+        const uint16_t* xr = X + (size_t)min(col, M - 1) * K + k0 + 8 * kg;
+        u32x4 wf[16], xf[16];
 #pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        wf[s] = *(const u32x4*)(wr + 32 * s);
-        xf[s] = *(const u32x4*)(xr + 32 * s);
+        for (int s = 0; s < 16; ++s) {
+            wf[s] = *(const u32x4*)(wr + 32 * s);
+            xf[s] = *(const u32x4*)(xr + 32 * s);
+        }
+        f32x4 acc = f32x4{};
+#pragma unroll
+        for (int s = 0; s < 16; ++s) acc = mfma16x16x32(as_bf16x8(xf[s]), as_bf16x8(wf[s]), acc);
+        // Lane (col, kg) holds rows 4 kg + i of its column.
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[wave][(4 * kg + i) * 16 + col] = acc[i];
     }
-    f32x4 acc = f32x4{};
-#pragma unroll
-    for (int s = 0; s < 16; ++s) acc = mfma16x16x32(as_bf16x8(xf[s]), as_bf16x8(wf[s]), acc);
-    // Lane (col, kg) holds rows 4 kg + i of its column.
-#pragma unroll
-    for (int i = 0; i < 4; ++i) red[wave][(4 * kg + i) * 16 + col] = acc[i];
+    if constexpr (MODE == 0) {
+        const bool extra = blockDim.x > 64 * (unsigned)nw;
+        if (rot && (wave == nw || !extra))
+            for (int t = extra ? lane : threadIdx.x; t < 8 * M; t += extra ? 64 : blockDim.x) {
+                const int pos = max(0, min(fq.lens[t >> 3], fq.cap - 1));
+                const double theta = pow(fq.base, -2.0 * ((j & 7) * 8 + (t & 7)) / D);
+                double sd, cd;
+                sincos((double)pos * theta, &sd, &cd);
+                cs_s[t] = make_float2((float)cd, (float)sd);
+            }
+    }
     __syncthreads();
     auto sum = [&](int row, int c) {
         float v = red[0][row * 16 + c];
@@ -329,10 +362,7 @@ __global__ __launch_bounds__(1024) void gemm_decode_fused_kernel(const uint16_t*
                 const int row = t >> 3, c = t & 7;
                 const int h = j >> 3, i = (j & 7) * 8 + c;
                 const int pos = max(0, min(fq.lens[row], fq.cap - 1));
-                const double theta = pow(fq.base, -2.0 * i / D);
-                double sd, cd;
-                sincos((double)pos * theta, &sd, &cd);
-                const float cs = (float)cd, sn = (float)sd;
+                const float cs = cs_s[t].x, sn = cs_s[t].y;
                 const float x1 = sum(row, c), x2 = sum(row, c + 8);
                 const float o1 = x1 * cs - x2 * sn, o2 = x2 * cs + x1 * sn;
                 if (h < fq.a) {
@@ -373,8 +403,10 @@ hipError_t gemm_decode_qkv_fused_bf16(const uint16_t* x, const WRows& w, int B, 
     if (!decode_fused_ok(B, N, K) || N != (a + (producer ? 2 * g : 0)) * 128) return hipErrorInvalidValue;
     if (pages.pt && (pages.n < 1 || pages.stride < 1 || cap != kPage * pages.stride)) return hipErrorInvalidValue;
     FusedQkv fq{q, kc, vc, lens, a, g, cap, producer ? 1 : 0, base, pages};
-    hipLaunchKernelGGL(gemm_decode_fused_kernel<0>, dim3(N / 16), dim3(64 * (K / 512)), 0, st, x, w, B, N, K, fq,
-                       FusedResid{});
+    const int waves = K / 512;
+    const bool extra = waves < 16 && N / 16 <= 256;
+    hipLaunchKernelGGL(gemm_decode_fused_kernel<0>, dim3(N / 16), dim3(64 * (waves + (extra ? 1 : 0))), 0, st, x, w, B,
+                       N, K, fq, FusedResid{});
     return hipGetLastError();
 }
 
