@@ -54,7 +54,7 @@
 namespace kvp {
 namespace {
 
-constexpr int BQ = 256, BKV = 128, D = 128, NT = 512;
+constexpr int BKV = 128, D = 128;
 constexpr float kLazy = 8.0f;
 
 typedef __attribute__((address_space(1))) void gvoid_t;
@@ -64,6 +64,10 @@ typedef __attribute__((address_space(3))) void lvoid_t;
 // (wave-uniform): lane i lands at lds_base + 16 i.
 __device__ __forceinline__ void load_lds_1k(const void* gsrc, void* lds_base) {
     __builtin_amdgcn_global_load_lds((gvoid_t*)gsrc, (lvoid_t*)lds_base, 16, 0, 0);
+}
+
+__device__ __forceinline__ void load_buf_1k(__amdgpu_buffer_rsrc_t r, u32x4* lds_base, uint32_t off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lvoid_t*)lds_base, 16, off, 0, 0, 0);
 }
 
 // Word 3 of a raw buffer resource: a valid (32-bit) data format, so that dword loads are
@@ -90,12 +94,14 @@ __device__ __forceinline__ void lgkm_wait(u32x4 (&f)[4]) {
     asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : "i"(N));
 }
 
-// 8 waves of 32 queries; two waves per SIMD (<= 256 registers each), 128 KB of LDS.
-template <bool PAGED>
-__global__ __launch_bounds__(NT, 2) void flash_prefill_kernel(
+// NW waves of 32 queries: 8, two per SIMD (<= 256 registers each), or 4; 128 KB of LDS.
+template <bool PAGED, int NW>
+__global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     uint16_t* __restrict__ O, float* __restrict__ lse, uint16_t* __restrict__ Ot, int Sp, int B, int S, int a,
     int g, int cap, float scale_log2, Pages pages) {
+    constexpr int BQ = 32 * NW, NT = 64 * NW;
+    constexpr int RPW = BKV / NW;   // rows of the K and of the V^T tile a wave requests
     // K: [stage][row * 16 + (chunk ^ (row & 15))]; V^T: [stage][d * 16 + (chunk ^ (d & 15))]
     // (rows of 256 bytes: 128 dims of a position, or 128 positions of a dim).
     __shared__ u32x4 lk[2][BKV * 16];
@@ -147,11 +153,11 @@ __global__ __launch_bounds__(NT, 2) void flash_prefill_kernel(
     const int slot_bytes = PAGED ? 0 : cap * D * 2;   // < 2^31: slots hold fewer than 2^23 positions
     const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)kbase, 0, slot_bytes, kRsrcWord3);
     const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((void*)vbase, 0, slot_bytes, kRsrcWord3);
-    uint32_t koff[4], voff[4];
+    uint32_t koff[RPW / 4], voff[RPW / 4];
     if constexpr (!PAGED) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = 16 * wave + 4 * j + (lane >> 4);
+        for (int j = 0; j < RPW / 4; ++j) {
+            const int r = RPW * wave + 4 * j + (lane >> 4);
             const int c = (lane & 15) ^ (r & 15);
             koff[j] = (uint32_t)(r * D + 8 * c) * 2u;
             voff[j] = (uint32_t)(r * cap + 8 * c) * 2u;
@@ -162,16 +168,16 @@ __global__ __launch_bounds__(NT, 2) void flash_prefill_kernel(
     const int last_q = min(qt * BQ + BQ - 1, S - 1);
     const int ntiles = last_q / BKV + 1;
 
-    // Issue the 32 + 32 one-kilobyte loads of tile t (4 + 4 per wave): K rows and V^T rows
-    // 16 wave + 4 j + lane / 16, four 256-byte rows per instruction.  Positions past the
+    // Issue the 32 + 32 one-kilobyte loads of tile t, shared by the waves: K rows and V^T rows
+    // RPW wave + 4 j + lane / 16, four 256-byte rows per instruction.  Positions past the
     // slot (only in the last tile when cap % 128 == 64) are clamped to the slot's last
     // row / chunk: they lie beyond S, so their scores are masked and their V is zeroed.
     // Paged: the tile's two pages are looked up once per tile (pages past the last one
     // holding a position < S are replaced by that page, so every read stays in a mapped
     // page; rows of positions >= S are masked and their V zeroed as above).  Each wave keeps
     // 64 consecutive entries of the table row in a register (lane i: entry 64 c + i) and
-    // reads the two entries with readlane: one table load per 32 tiles.  Wave w's K rows
-    // 16 w .. 16 w + 15 all lie in page w / 4 of the tile, so its K base is wave-uniform.
+    // reads the two entries with readlane: one table load per 32 tiles.  A wave's K rows all lie
+    // in one page of the tile, so its K base is wave-uniform.
     int pchunk = -1, pgv = 0;
     auto issue_tile = [&](int t, int stg) {
         const int t0 = t * BKV;
@@ -186,15 +192,15 @@ __global__ __launch_bounds__(NT, 2) void flash_prefill_kernel(
             const int pg0 = min(max(__builtin_amdgcn_readlane(pgv, p0 & 63), 0), pages.n - 1);
             const int pg1 = min(max(__builtin_amdgcn_readlane(pgv, p1 & 63), 0), pages.n - 1);
             const size_t hb = (size_t)kvh * pages.n;
-            const uint16_t* kw = Kc + (hb + (wave >= 4 ? pg1 : pg0)) * kPage * D;
+            const uint16_t* kw = Kc + (hb + (wave >= NW / 2 ? pg1 : pg0)) * kPage * D;
             const uint16_t* v0 = Vc + (hb + pg0) * D * kPage;
             const uint16_t* v1 = Vc + (hb + pg1) * D * kPage;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = 16 * wave + 4 * j + (lane >> 4);
+            for (int j = 0; j < RPW / 4; ++j) {
+                const int r = RPW * wave + 4 * j + (lane >> 4);
                 const int c = (lane & 15) ^ (r & 15);
-                load_lds_1k(kw + (size_t)(r & (kPage - 1)) * D + 8 * c, &lk[stg][(16 * wave + 4 * j) * 16]);
-                load_lds_1k((c >= 8 ? v1 : v0) + r * kPage + 8 * (c & 7), &lv[stg][(16 * wave + 4 * j) * 16]);
+                load_lds_1k(kw + (size_t)(r & (kPage - 1)) * D + 8 * c, &lk[stg][(RPW * wave + 4 * j) * 16]);
+                load_lds_1k((c >= 8 ? v1 : v0) + r * kPage + 8 * (c & 7), &lv[stg][(RPW * wave + 4 * j) * 16]);
             }
             return;
         }
@@ -204,11 +210,9 @@ __global__ __launch_bounds__(NT, 2) void flash_prefill_kernel(
         // and their V is zeroed.
         const int wu = __builtin_amdgcn_readfirstlane(wave);   // LDS destinations are scalar
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lvoid_t*)&lk[stg][(16 * wu + 4 * j) * 16], 16,
-                                                     koff[j] + (uint32_t)t0 * (D * 2), 0, 0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lvoid_t*)&lv[stg][(16 * wu + 4 * j) * 16], 16,
-                                                     voff[j] + (uint32_t)t0 * 2, 0, 0, 0);
+        for (int j = 0; j < RPW / 4; ++j) {
+            load_buf_1k(krs, &lk[stg][(RPW * wu + 4 * j) * 16], koff[j] + (uint32_t)t0 * (D * 2));
+            load_buf_1k(vrs, &lv[stg][(RPW * wu + 4 * j) * 16], voff[j] + (uint32_t)t0 * 2);
         }
     };
     auto fix_tail = [&](int t, int stg) {
@@ -437,16 +441,30 @@ hipError_t flash_prefill_bf16(const uint16_t* q, const uint16_t* kc, const uint1
                               uint16_t* o, float* lse, uint16_t* ot, int Sp, int B, int S, int a, int g,
                               int cap, const Pages& pages, hipStream_t st) {
     if (ot && (pages.pt || S % 8 != 0)) return hipErrorInvalidValue;
-    const int nqt = (S + BQ - 1) / BQ;
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
+    // 8 waves (256 queries) share each key tile, half the LDS fills and barriers per product: a
+    // workgroup takes 3.0 us a tile.  4 waves (128 queries) still take 2.7 us, since one wave
+    // alone on a SIMD waits as long for its own reads: better only while every workgroup of
+    // them has a CU to itself.  Both give the same bits.  Measured (us, 8 / 4 waves): 16 heads,
+    // 1000 tokens 30.4 / 27.9, 3000 tokens 71.9 / 65.5; 48 heads, 1000 tokens (384 workgroups
+    // of 4 waves) 32.9 / 34.4; 16 heads, 6000 tokens 157 / 227.
+    const bool wide = (int64_t)((S + 127) / 128) * a * B > 256;
+    const int bq = wide ? 256 : 128;
+    const dim3 grid((S + bq - 1) / bq * a * B), block(2 * bq);
+#define KVP_FLASH(PG, OT)                                                                                         \
+    if (wide)                                                                                                     \
+        hipLaunchKernelGGL((flash_prefill_kernel<PG, 8>), grid, block, 0, st, q, kc, vc, o, lse, OT, Sp, B, S, a, \
+                           g, cap, scale_log2, pages);                                                            \
+    else                                                                                                          \
+        hipLaunchKernelGGL((flash_prefill_kernel<PG, 4>), grid, block, 0, st, q, kc, vc, o, lse, OT, Sp, B, S, a, \
+                           g, cap, scale_log2, pages)
     if (pages.pt) {
         if (pages.n < 1 || pages.stride < 1 || S > kPage * pages.stride) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(flash_prefill_kernel<true>, dim3(nqt * a * B), dim3(NT), 0, st, q, kc, vc, o, lse,
-                           nullptr, Sp, B, S, a, g, cap, scale_log2, pages);
+        KVP_FLASH(true, nullptr);
     } else {
-        hipLaunchKernelGGL(flash_prefill_kernel<false>, dim3(nqt * a * B), dim3(NT), 0, st, q, kc, vc, o, lse,
-                           ot, Sp, B, S, a, g, cap, scale_log2, pages);
+        KVP_FLASH(false, ot);
     }
+#undef KVP_FLASH
     return hipGetLastError();
 }
 

@@ -27,6 +27,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace kvp {
 namespace {
@@ -273,8 +274,8 @@ __global__ __launch_bounds__(kBigNT, 2) void gemm_big(const uint16_t* __restrict
     vm_wait<0>();
     // Pass i: rows 128 i .. + 127 of the tile.
     char* st = (char*)&lds[0];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    auto pass = [&](auto i_t) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_t)::value;
         __syncthreads();   // the LDS is free: last fragment reads / previous flush are done
         typename Epi::template Pre<128, BN, kBigNT> pre;
 #pragma unroll
@@ -286,7 +287,9 @@ __global__ __launch_bounds__(kBigNT, 2) void gemm_big(const uint16_t* __restrict
         epi.template prefetch<128, BN, kBigNT>(m0 + 128 * i, n0, tid, M, N, pre);
         __syncthreads();
         epi.template flush<128, BN, kBigNT>(m0 + 128 * i, n0, tid, M, N, st, pre);
-    }
+    };
+    pass(std::integral_constant<int, 0>{});
+    pass(std::integral_constant<int, 1>{});
 }
 
 // 128 x 256 tile, the first of gemm_big's two phases alone: 64 x 64 per wave, 16 products a

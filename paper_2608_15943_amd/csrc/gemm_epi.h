@@ -97,33 +97,44 @@ struct QkvEpi {
             if (reg < 0) continue;
             const int c0 = 2 * HALF * hb;     // the head block's first staged column
             if (reg == 2) {
-                // V^T: item (column n, positions 8 k .. 8 k + 7), consecutive lanes along k.
+                // V^T: item (column n, 8 rows from d0 + 8 k), consecutive lanes along k.  d0 moves
+                // the runs to positions that are multiples of 8, aligned in the slot and inside
+                // one page; the d0 rows before the first run follow one value a lane, and a run
+                // that leaves the pass, the sequence or M goes out value by value.  (Eight
+                // 2-byte stores, or misaligned 16-byte ones, for every run made the epilogue of
+                // 2 x 777 tokens 14 us longer.)
                 constexpr int KC = ROWS / 8, TV = KC * 2 * HALF / NT;
+                const int s0 = m0 % o.S, d0 = (8 - s0 % 8) % 8;
+                auto dim_of = [&](int n) { return BN == 64 ? sub + (n & 31) + 2 * (n & 32) : n; };
+                auto put = [&](int m, int n, float x) {
+                    const int b = m / o.S;
+                    o.vc[v_at(b, head, dim_of(n), m - b * o.S)] = f2bf(x);
+                };
 #pragma unroll
                 for (int t = 0; t < TV; ++t) {
                     const int id = tid + NT * t;
-                    const int k = id % KC, n = id / KC;
-                    const int m = m0 + 8 * k;
+                    const int r = 8 * (id % KC) + d0, n = id / KC;
+                    const int m = m0 + r;
                     if (m >= M) continue;
                     float x[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] = *(const float*)(st + st_off<BN>(8 * k + e, c0 + n));
-                    const u32x4 v = {pack2bf(x[0], x[1]), pack2bf(x[2], x[3]), pack2bf(x[4], x[5]), pack2bf(x[6], x[7])};
-                    const int dim = BN == 64 ? sub + (n & 31) + 2 * (n & 32) : n;
+                    for (int e = 0; e < 8; ++e)
+                        x[e] = *(const float*)(st + st_off<BN>(min(r + e, ROWS - 1), c0 + n));
                     const int b = m / o.S, s = m - b * o.S;
-                    if (s + 8 <= o.S && m + 8 <= M && (!o.pages.pt || s % kPage <= kPage - 8)) {
-                        // One run of 8 positions of a sequence (and of a page): a 16-byte store
-                        // even where s is odd (global memory takes any alignment; eight 2-byte
-                        // stores made the epilogue 10 us longer at S = 777).
-                        __builtin_memcpy(o.vc + v_at(b, head, dim, s), &v, 16);
+                    if (s % 8 == 0 && s + 8 <= o.S && r + 8 <= ROWS && m + 8 <= M) {
+                        *(u32x4*)(o.vc + v_at(b, head, dim_of(n), s)) =
+                            u32x4{pack2bf(x[0], x[1]), pack2bf(x[2], x[3]), pack2bf(x[4], x[5]), pack2bf(x[6], x[7])};
                     } else {
-                        for (int e = 0; e < 8 && m + e < M; ++e) {
-                            int bb = b, ss = s + e;
-                            while (ss >= o.S) { ss -= o.S; ++bb; }
-                            o.vc[v_at(bb, head, dim, ss)] = (bf16_t)(v[e >> 1] >> (16 * (e & 1)));
-                        }
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (r + e < ROWS && m + e < M) put(m + e, n, x[e]);
                     }
                 }
+                if (d0)
+                    for (int id = tid; id < 8 * 2 * HALF; id += NT) {
+                        const int e = id % 8, n = id / 8;
+                        if (e < d0 && m0 + e < M) put(m0 + e, n, *(const float*)(st + st_off<BN>(e, c0 + n)));
+                    }
                 continue;
             }
 #pragma unroll
