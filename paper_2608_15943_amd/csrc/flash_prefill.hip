@@ -16,6 +16,8 @@
 // which 16-byte chunk each lane fetches.  Eight waves sharing 128-position tiles
 // halve both the global->LDS bytes and the barriers per FLOP compared with four
 // waves on 64-position tiles (measured: 10 % faster on the 8-layer stage share).
+// Small grids (the rule is at the launch): 128 queries, waves w and w + 4 share 32 of them and
+// take the first and the second half of every key tile; the halves' sums meet in LDS.
 //
 // Per tile and wave:
 //   S^T[128 x 32] = K_tile Q^T  v_mfma_f32_32x32x16_bf16, A = K rows from LDS,
@@ -94,13 +96,41 @@ __device__ __forceinline__ void lgkm_wait(u32x4 (&f)[4]) {
     asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : "i"(N));
 }
 
-// NW waves of 32 queries: 8, two per SIMD (<= 256 registers each), or 4; 128 KB of LDS.
-template <bool PAGED, int NW>
-__global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
+// Eight fragments at once, with their wait (the other wave of the SIMD runs meanwhile):
+// K steps a0 .. a3 of two blocks, or V^T chunks a0, a1 of the four d blocks.
+template <int OFF>
+__device__ __forceinline__ void read_k(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x4 (&f)[8]) {
+    asm volatile("ds_read_b128 %0, %8 offset:%12\n\tds_read_b128 %1, %8 offset:%13\n\t"
+                 "ds_read_b128 %2, %9 offset:%12\n\tds_read_b128 %3, %9 offset:%13\n\t"
+                 "ds_read_b128 %4, %10 offset:%12\n\tds_read_b128 %5, %10 offset:%13\n\t"
+                 "ds_read_b128 %6, %11 offset:%12\n\tds_read_b128 %7, %11 offset:%13\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]),
+                   "=&v"(f[7])
+                 : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "i"(OFF), "i"(OFF + 8192));
+}
+template <int OFF>
+__device__ __forceinline__ void read_v(uint32_t a0, uint32_t a1, u32x4 (&f)[8]) {
+    asm volatile("ds_read_b128 %0, %8 offset:%10\n\tds_read_b128 %1, %8 offset:%11\n\t"
+                 "ds_read_b128 %2, %8 offset:%12\n\tds_read_b128 %3, %8 offset:%13\n\t"
+                 "ds_read_b128 %4, %9 offset:%10\n\tds_read_b128 %5, %9 offset:%11\n\t"
+                 "ds_read_b128 %6, %9 offset:%12\n\tds_read_b128 %7, %9 offset:%13\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]),
+                   "=&v"(f[7])
+                 : "v"(a0), "v"(a1), "i"(OFF), "i"(OFF + 8192), "i"(OFF + 16384), "i"(OFF + 24576));
+}
+
+// 8 waves, two per SIMD (<= 256 registers each); 128 KB of LDS.  KS == 1: 8 x 32 queries, every
+// wave takes the whole key tile.  KS == 2: 4 x 32 queries; waves 0 .. 3 take the first half of
+// every key tile, waves 4 .. 7 the second half, and their sums are merged at the end.
+template <bool PAGED, int KS>
+__global__ __launch_bounds__(512, 2) void flash_prefill_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     uint16_t* __restrict__ O, float* __restrict__ lse, uint16_t* __restrict__ Ot, int Sp, int B, int S, int a,
     int g, int cap, float scale_log2, Pages pages) {
-    constexpr int BQ = 32 * NW, NT = 64 * NW;
+    constexpr int NW = 8, BQ = 32 * NW / KS, NT = 64 * NW;
+    constexpr int KB = 4 / KS;      // 32-key blocks of a tile per wave
     constexpr int RPW = BKV / NW;   // rows of the K and of the V^T tile a wave requests
     // K: [stage][row * 16 + (chunk ^ (row & 15))]; V^T: [stage][d * 16 + (chunk ^ (d & 15))]
     // (rows of 256 bytes: 128 dims of a position, or 128 positions of a dim).
@@ -134,7 +164,8 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
     const int kvh = head / (a / g);
 
     const int ldq = a * D;
-    const int q0w = qt * BQ + wave * 32;         // first query of this wave
+    const int qw = KS == 1 ? wave : wave & 3, kw = KS == 1 ? 0 : wave >> 2;   // queries, half of the keys
+    const int q0w = qt * BQ + qw * 32;           // first query of this wave
     const int q_lane = q0w + l32;                // the query whose column this lane holds
 
     // Q^T fragments: 8 k-steps of 16 dims, lane holds dims 16 ks + 8 hi + 0..7.
@@ -192,14 +223,14 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
             const int pg0 = min(max(__builtin_amdgcn_readlane(pgv, p0 & 63), 0), pages.n - 1);
             const int pg1 = min(max(__builtin_amdgcn_readlane(pgv, p1 & 63), 0), pages.n - 1);
             const size_t hb = (size_t)kvh * pages.n;
-            const uint16_t* kw = Kc + (hb + (wave >= NW / 2 ? pg1 : pg0)) * kPage * D;
+            const uint16_t* kp = Kc + (hb + (wave >= NW / 2 ? pg1 : pg0)) * kPage * D;
             const uint16_t* v0 = Vc + (hb + pg0) * D * kPage;
             const uint16_t* v1 = Vc + (hb + pg1) * D * kPage;
 #pragma unroll
             for (int j = 0; j < RPW / 4; ++j) {
                 const int r = RPW * wave + 4 * j + (lane >> 4);
                 const int c = (lane & 15) ^ (r & 15);
-                load_lds_1k(kw + (size_t)(r & (kPage - 1)) * D + 8 * c, &lk[stg][(RPW * wave + 4 * j) * 16]);
+                load_lds_1k(kp + (size_t)(r & (kPage - 1)) * D + 8 * c, &lk[stg][(RPW * wave + 4 * j) * 16]);
                 load_lds_1k((c >= 8 ? v1 : v0) + r * kPage + 8 * (c & 7), &lv[stg][(RPW * wave + 4 * j) * 16]);
             }
             return;
@@ -236,12 +267,13 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
     // LDS byte addresses of this lane's fragments in stage 0: K step ks of block 0 (block mb is
     // 8 KB further, since rows 32 mb + ksw share ksw's swizzle) and V^T chunk c of d block 0
     // (d blocks are 8 KB apart likewise); stage 1 is 32 KB further.
-    uint32_t kaddr[8], vaddr[8];
+    uint32_t kaddr[8], vaddr[2 * KB];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-        kaddr[ks] = (uint32_t)(uintptr_t)&lk[0][ksw * 16 + ((2 * ks + hi) ^ (ksw & 15))];
-        vaddr[ks] = (uint32_t)(uintptr_t)&lv[0][l32 * 16 + ((2 * ks + hi) ^ (l32 & 15))];
-    }
+    for (int ks = 0; ks < 8; ++ks)
+        kaddr[ks] = (uint32_t)(uintptr_t)&lk[0][(32 * KB * kw + ksw) * 16 + ((2 * ks + hi) ^ (ksw & 15))];
+#pragma unroll
+    for (int c = 0; c < 2 * KB; ++c)
+        vaddr[c] = (uint32_t)(uintptr_t)&lv[0][l32 * 16 + ((2 * (2 * KB * kw + c) + hi) ^ (l32 & 15))];
     issue_tile(0, 0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -258,26 +290,39 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
         const bool more = t + 1 < ntiles;
         bool issued = false;
 
-        const int t0 = t * BKV;
+        const int t0 = t * BKV + 32 * KB * kw;   // first key of this wave
         // The tile body; on a tile that holds this wave's diagonal (or the end of the
         // sequence) the 32-key blocks with no visible key skip their MFMAs.
         auto body = [&](auto diag_t) {
             constexpr bool kDiag = decltype(diag_t)::value;
-            int nmb = 4;
-            if constexpr (kDiag) nmb = min(min(4, (q0w + 31 - t0) / 32 + 1), (S - t0 + 31) / 32);
+            int nmb = KB;
+            if constexpr (kDiag) nmb = min(min(KB, (q0w + 31 - t0) / 32 + 1), (S - t0 + 31) / 32);
             // ---- S^T = K Q^T: 32 MFMAs, each K fragment read once ------------------------
-            f32x16 s[4] = {f32x16{}, f32x16{}, f32x16{}, f32x16{}};
+            f32x16 s[KB];
+#pragma unroll
+            for (int mb = 0; mb < KB; ++mb) s[mb] = f32x16{};
             auto kfrag = [&](int mb, int ks) {
-                const int row = 32 * mb + ksw;
+                const int row = 32 * (KB * kw + mb) + ksw;
                 return as_bf16x8(lk[stg][row * 16 + ((2 * ks + hi) ^ (row & 15))]);
             };
             if constexpr (kDiag) {
 #pragma unroll
-                for (int mb = 0; mb < 4; ++mb)
+                for (int mb = 0; mb < KB; ++mb)
                     if (mb < nmb) {
 #pragma unroll
                         for (int ks = 0; ks < 8; ++ks) s[mb] = mfma32x32x16(kfrag(mb, ks), qf[ks], s[mb]);
                     }
+            } else if constexpr (KS == 2) {
+                u32x4 kf[8];
+                auto mul = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        s[i & 1] = mfma32x32x16(as_bf16x8(kf[i]), qf[k0 + (i >> 1)], s[i & 1]);
+                };
+                read_k<stg * 32768>(kaddr[0], kaddr[1], kaddr[2], kaddr[3], kf);
+                mul(0);
+                read_k<stg * 32768>(kaddr[4], kaddr[5], kaddr[6], kaddr[7], kf);
+                mul(4);
             } else if constexpr (PAGED) {
 #pragma unroll
             for (int ks = 0; ks < 8; ++ks) {
@@ -316,7 +361,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
                 // lane's positions is at most lim (one compare against a constant each).
                 const int lim = min(q_lane, S - 1) - t0 - 8 * hi;
 #pragma unroll
-                for (int mb = 0; mb < 4; ++mb)
+                for (int mb = 0; mb < KB; ++mb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
                         if (32 * mb + 16 * (i >> 3) + (i & 7) > lim) s[mb][i] = -INFINITY;
@@ -324,7 +369,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
             // ---- online softmax -------------------------------------------------------
             float mx = -INFINITY;
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
+            for (int mb = 0; mb < KB; ++mb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[mb][i]);
             mx = pair32_max(mx);
@@ -337,15 +382,17 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
 #pragma unroll
                 for (int db = 0; db < 4; ++db) o[db] *= alpha;
             }
-            bf16x8 pb[4][2];
+            // The second half's first scores may all be -inf: their weights are 0, not NaN.
+            const float m_sub = KS == 2 && kw && m_run == -INFINITY ? 0.f : m_run;
+            bf16x8 pb[KB][2];
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
+            for (int mb = 0; mb < KB; ++mb)
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
                     float e[8];
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
-                        e[k] = __builtin_amdgcn_exp2f(fmaf(s[mb][8 * p + k], scale_log2, -m_run));
+                        e[k] = __builtin_amdgcn_exp2f(fmaf(s[mb][8 * p + k], scale_log2, -m_sub));
                         l_run += e[k];
                     }
                     u32x4 w;
@@ -356,15 +403,26 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
                     pb[mb][p] = as_bf16x8(w);
                 }
             // ---- O^T += V^T P^T: 32 MFMAs over 8 chunks of 16 positions -------------------
-            if constexpr (kDiag || PAGED) {
+            if constexpr (KS == 2 && !kDiag) {
+                u32x4 vf[8];
+                auto mul = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
+                    for (int i = 0; i < 8; ++i)
+                        o[i & 3] = mfma32x32x16(as_bf16x8(vf[i]), pb[c0 >> 1][i >> 2], o[i & 3]);
+                };
+                read_v<stg * 32768>(vaddr[0], vaddr[1], vf);
+                mul(0);
+                read_v<stg * 32768>(vaddr[2], vaddr[3], vf);
+                mul(2);
+            } else if constexpr (kDiag || PAGED) {
+#pragma unroll
+            for (int c = 0; c < 2 * KB; ++c) {
                 const int mb = c >> 1, p = c & 1;
                 if (kDiag && mb >= nmb) continue;
 #pragma unroll
                 for (int db = 0; db < 4; ++db) {
                     const int d = 32 * db + l32;
-                    const bf16x8 vf = as_bf16x8(lv[stg][d * 16 + ((2 * c + hi) ^ (d & 15))]);
+                    const bf16x8 vf = as_bf16x8(lv[stg][d * 16 + ((2 * (2 * KB * kw + c) + hi) ^ (d & 15))]);
                     o[db] = mfma32x32x16(vf, pb[mb][p], o[db]);
                 }
             }
@@ -389,7 +447,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
             }
         };
         if (t0 <= q0w + 31 && q0w < S) {          // some key of the tile is visible to this wave
-            if ((t0 + BKV - 1 > q0w) || (t0 + BKV > S)) body(std::true_type{});
+            if ((t0 + 32 * KB - 1 > q0w) || (t0 + 32 * KB > S)) body(std::true_type{});
             else body(std::false_type{});
         }
         if (more && !issued) issue_tile(t + 1, stg ^ 1);   // this wave saw no key of tile t
@@ -413,8 +471,36 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void flash_prefill_kernel(
     // Lanes q and q ^ 32 hold the same query, so both take this branch or neither.  The
     // token-major copy (training) is staged in the K buffers, free once every wave is past
     // its last tile.
-    uint16_t* ts = (uint16_t*)&lk[0][0] + wave * (D * 32);
-    if (Ot) __syncthreads();
+    uint16_t* ts = (uint16_t*)(KS == 1 ? &lk[0][0] : &lv[0][0]) + qw * (D * 32);
+    if constexpr (KS == 2) {
+        // Sums of the second half of the keys through LDS: O in the K buffers (64 KB), maxima and
+        // sums in the upper V^T buffer, which the copies staged in the lower one do not reach.
+        f32x4* so = (f32x4*)&lk[0][0] + qw * (16 * 64) + lane;
+        float2* sm = (float2*)&lv[1][0] + qw * 64 + lane;
+        __syncthreads();   // every wave is past its last tile
+        if (kw) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                so[64 * i] = f32x4{o[i >> 2][4 * (i & 3)], o[i >> 2][4 * (i & 3) + 1], o[i >> 2][4 * (i & 3) + 2],
+                                   o[i >> 2][4 * (i & 3) + 3]};
+            *sm = make_float2(m_run, l_run);
+        }
+        __syncthreads();
+        if (kw) return;
+        const float2 ml = *sm;
+        const float m = fmaxf(m_run, ml.x);
+        const float f0 = __builtin_amdgcn_exp2f(m_run - m), f1 = __builtin_amdgcn_exp2f(ml.x - m);
+        m_run = m;
+        l_run = l_run * f0 + ml.y * f1;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const f32x4 v = so[64 * i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[i >> 2][4 * (i & 3) + e] = o[i >> 2][4 * (i & 3) + e] * f0 + v[e] * f1;
+        }
+    } else if (Ot) {
+        __syncthreads();
+    }
     if (q_lane < S) {
         const float l_tot = pair32_sum(l_run);
         const float inv = 1.0f / l_tot;
@@ -442,21 +528,27 @@ hipError_t flash_prefill_bf16(const uint16_t* q, const uint16_t* kc, const uint1
                               int cap, const Pages& pages, hipStream_t st) {
     if (ot && (pages.pt || S % 8 != 0)) return hipErrorInvalidValue;
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
-    // 8 waves (256 queries) share each key tile, half the LDS fills and barriers per product: a
-    // workgroup takes 3.0 us a tile.  4 waves (128 queries) still take 2.7 us, since one wave
-    // alone on a SIMD waits as long for its own reads: better only while every workgroup of
-    // them has a CU to itself.  Both give the same bits.  Measured (us, 8 / 4 waves): 16 heads,
-    // 1000 tokens 30.4 / 27.9, 3000 tokens 71.9 / 65.5; 48 heads, 1000 tokens (384 workgroups
-    // of 4 waves) 32.9 / 34.4; 16 heads, 6000 tokens 157 / 227.
-    const bool wide = (int64_t)((S + 127) / 128) * a * B > 256;
+    // A workgroup of 256 queries takes 2.5 us a key tile, one of 128 queries with the keys split
+    // 1.7 us (both plus about 9 us): the split is better while the longest workgroup, not the
+    // sum of them, decides.  That holds while each of its workgroups has a CU to itself, and up
+    // to two per CU (the longest start first) from about 1000 positions on; below that, and
+    // beyond two, it pays twice the LDS fills per query for nothing.  Measured (us, 256 queries
+    // / 128 split; S x heads of all sequences): 200 x 32 13.6 / 11.9, 1000 x 16 29.8 / 22.9,
+    // 2048 x 16 49.5 / 36.4, 777 x 32 25.0 / 20.3, 1000 x 32 30.9 / 23.9; more than 256
+    // workgroups: 3000 x 16 68.9 / 49.8, 4096 x 16 95.1 / 79.8, 2048 x 32 55.0 / 48.9, 1000 x 48
+    // 30.6 / 29.4, 1000 x 64 35.5 / 35.3, 512 x 96 22.6 / 24.5; more than 512: 6000 x 16 155 / 181,
+    // 3000 x 32 83.5 / 93.7, 2048 x 48 59.2 / 72.3.  (4 waves of 128 queries, unsplit, 2.7 us a
+    // tile: 1000 x 16 27.9, 3000 x 16 65.5.)
+    const int64_t narrow = (int64_t)((S + 127) / 128) * a * B;   // workgroups of 128 queries
+    const bool wide = narrow > (S > 7 * 128 ? 512 : 256);
     const int bq = wide ? 256 : 128;
-    const dim3 grid((S + bq - 1) / bq * a * B), block(2 * bq);
+    const dim3 grid((S + bq - 1) / bq * a * B), block(512);
 #define KVP_FLASH(PG, OT)                                                                                         \
     if (wide)                                                                                                     \
-        hipLaunchKernelGGL((flash_prefill_kernel<PG, 8>), grid, block, 0, st, q, kc, vc, o, lse, OT, Sp, B, S, a, \
+        hipLaunchKernelGGL((flash_prefill_kernel<PG, 1>), grid, block, 0, st, q, kc, vc, o, lse, OT, Sp, B, S, a, \
                            g, cap, scale_log2, pages);                                                            \
     else                                                                                                          \
-        hipLaunchKernelGGL((flash_prefill_kernel<PG, 4>), grid, block, 0, st, q, kc, vc, o, lse, OT, Sp, B, S, a, \
+        hipLaunchKernelGGL((flash_prefill_kernel<PG, 2>), grid, block, 0, st, q, kc, vc, o, lse, OT, Sp, B, S, a, \
                            g, cap, scale_log2, pages)
     if (pages.pt) {
         if (pages.n < 1 || pages.stride < 1 || S > kPage * pages.stride) return hipErrorInvalidValue;

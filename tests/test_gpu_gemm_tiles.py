@@ -2,7 +2,8 @@
 that take each tile, with row and column remainders of it (rows that fill no tile, an odd
 number of heads so that the last column tile is half empty), against the fp64 oracle at the
 bf16 tolerance; and, since every tile sums K in the same order, the same sequence alone and
-inside a large batch gives the same bits."""
+inside a large batch gives the same bits, but for the attention, which splits the keys of a
+small grid: its outputs agree within their roundings, and the rest is compared through them."""
 import numpy as np
 import pytest
 import torch
@@ -36,6 +37,14 @@ def _forward(dm, B, S):
     return y, o
 
 
+def assert_attention_close(o1, o, V, a, g):
+    """Two attention outputs [S][a * 128] of the same scores, summed over different splits of the
+    keys: each weight is rounded to bf16 (8 bits: 2^-8 of it, so 2^-8 max|V| of the output) and so
+    is the output, in both."""
+    vmax = V.float().abs().amax((1, 2)).repeat_interleave(a // g * 128)   # per column of o
+    assert ((o1.float() - o.float()).abs() <= 1.01 * 2.0**-6 * vmax).all()
+
+
 @pytest.mark.parametrize("a,g,B,S", [
     (1, 1, 1, 1),        # one row, 64-wide tiles
     (3, 1, 1, 63),
@@ -65,5 +74,30 @@ def test_layer_forward_over_the_tile_sizes(a, g, B, S):
         assert rel_err(to_np(V[b, :, :, :S]).transpose(0, 2, 1), caches[0][1]) <= tol(w), b
     assert torch.isfinite(y.float()).all() and torch.isfinite(o.float()).all()
     y1, o1 = _forward(dm, 1, S)
-    assert torch.equal(y1[0], y[0]) and torch.equal(o1[0], o[0])
+    assert_attention_close(o1[0], o[0], V[0, :, :, :S], a, g)
+    same = (o1[0] == o[0]).all(1)
+    assert same[:64].all()   # queries that see no key of a second half
+    assert torch.equal(y1[0][same], y[0][same])
+    # Elsewhere y differs by what o does, and the two roundings of y to bf16 (8 bits: 2^-8 each).
+    do = (o1[0].double() - o[0].double()).abs().cpu()
+    bound = do @ torch.from_numpy(np.abs(np.asarray(ow[0].wo, dtype=np.float64))).T + 2.0**-7 * y[0].double().abs().cpu()
+    assert ((y1[0].double() - y[0].double()).abs().cpu() <= 1.01 * bound + 1e-5).all()
     assert torch.equal(dm.slots[0][0][0], K[0]) and torch.equal(dm.slots[0][1][0], V[0])
+
+
+@pytest.mark.parametrize("S", [64, 65, 128, 129, 191, 193, 256, 385, 900])
+def test_attention_with_split_keys(S):
+    """Lengths around the halves of a key tile and around a workgroup's 128 queries: the first
+    sequence alone (keys split) against the oracle and against the same sequence in a batch
+    large enough for unsplit workgroups."""
+    a, g = 3, 1
+    B = 512 // (a * ((S + 127) // 128)) + 1
+    w = small_workload("split-keys", 1, a * 128, a, g, [0])
+    say(f"[split keys] S={S} B={B}")
+    dm = build_device_model(w, B, S, (S + 63) // 64 * 64)
+    y1, o1 = _forward(dm, 1, S)
+    ref, _, _, _ = oat.stack_prefill(ki.prefill_x(w, [0], np.arange(S))[0], oracle_weights(w), w.tau, a, g, w.d_h,
+                                     w.rope_base)
+    assert rel_err(to_np(y1[0]), ref) <= tol(w)
+    _, o = _forward(dm, B, S)
+    assert_attention_close(o1[0], o[0], dm.slots[0][1][0, :, :, :S], a, g)
