@@ -286,7 +286,8 @@ int kvp_set_kv_slot(kvp_ctx* ctx, int l, void* K, void* V);
  * workspace holds Q, the attention output, the fp32 residual stream and its
  * bf16 copy, the RoPE table (prefill) and split-K partial results (decode);
  * for KVP_PHASE_BACKWARD the gradients in flight, (bf16 models) their
- * transposed copies and transposed weights, (fp32 models) the per-(token,
+ * transposed copies and transposed weights and the partial sums of weight
+ * gradients or of dK/dV that several workgroups share, (fp32 models) the per-(token,
  * head) softmax statistics, and the producers' fp32 dK/dV sums.
  * Errors: KVP_E_INVALID_ARG, KVP_E_CAPACITY (B > max_batch, S > max_seq).
  */
