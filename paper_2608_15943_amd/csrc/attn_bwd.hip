@@ -12,9 +12,11 @@
 // Kernels:
 //   attn_bwd_prep    D = rowsum(dO * O) per (token, head).
 //   transpose_bf16   operands of the dO, dX and weight-gradient products.
-//   flash_bwd_kv     one workgroup per (sequence, KV head, 256 keys); loops over the r
+//   flash_bwd_kv     256 keys of one (sequence, KV head) per workgroup; loops over the r
 //                    query heads of the group and the query blocks at or after its
-//                    keys; dK, dV accumulate in registers.
+//                    keys; dK, dV accumulate in registers.  A small launch deals the query
+//                    blocks of a key block in chunks to several workgroups (kv_plan).
+//   kv_reduce        adds the chunks' sums, then the epilogue of the unsplit kernel.
 //   flash_bwd_q      one workgroup per (sequence, head, 256 queries); loops over the
 //                    key blocks at or before its queries; dQ accumulates in registers.
 //
@@ -835,11 +837,16 @@ __global__ __launch_bounds__(Q_NT, 2) void flash_bwd_q_kernel(QArgs A) {
         tm_flush(ts, A.out_t, (size_t)A.B * A.S, head * D, (size_t)b * A.S + q0w, A.S - q0w, lane);
 }
 
-// Workgroups of the dK, dV launch.  One per key block and (sequence, KV head) when that makes
-// two rounds of the 256 CUs or more; else the query blocks (3.4 us each for a workgroup) are
-// dealt in chunks so that about 512 workgroups share them, at least 4 blocks each, and
-// kv_reduce adds the chunks.  Measured at 2 x 777 tokens, 16/8 heads: 64 workgroups of up to
-// 26 blocks took 88 us, 256 of at most 4 take 26 and their sum 16.
+// Workgroups of the dK, dV launch: one per key block and (sequence, KV head), longest first,
+// unless the longest has more query blocks than four thirds of a CU's share (and more than 4):
+// then no workgroup takes more than that, and kv_reduce adds the chunks.  A smaller chunk
+// leaves no CUs for the blocks' remainders and writes more sums.  Measured (us, whole / chunks
+// of 4/3 of the share / of 1/2, as of 512 workgroups; B x S, heads): 1 x 300, 16/8 41 / 25 / 25;
+// 2 x 777 85 / 38 / 38; 3 x 1000 104 / 58 / 78; 1 x 4096 377 / 177 / 218; 2 x 4096 412 / 351 / 389;
+// 3 x 3000 316 / 278 / 310; 1 x 8000, 64/8 3480 / 2850 / 2800.  Whole by this rule: 12 x 1000
+// 138 / - / 189; 7 x 2000 281 / - / 317; 3 x 5000 618 / - / 720; 2 x 6000 645 / - / 700;
+// 2 x 4000, 16/16 263 / - / 312.
+constexpr int kKvCus = 256, kKvSlots = 384;
 struct KvPlan {
     int chunk, groups;
 };
@@ -847,12 +854,16 @@ KvPlan kv_plan(int B, int S, int a, int g) {
     const int Sp = (S + 63) / 64 * 64, r = a / g, nkb = (S + KV_BK - 1) / KV_BK, G = B * g;
     int64_t blocks = 0;
     for (int kb = 0; kb < nkb; ++kb) blocks += kv_blocks(kb, Sp, r);
-    if ((int64_t)nkb * G >= 512) return {0, nkb * G};
-    const int chunk = std::max(4, (int)((blocks * G + 511) / 512));
-    if (kv_blocks(0, Sp, r) < 2 * chunk) return {0, nkb * G};
-    int n = 0;
-    for (int kb = 0; kb < nkb; ++kb) n += (kv_blocks(kb, Sp, r) + chunk - 1) / chunk;
-    return {chunk, n * G};
+    const KvPlan whole{0, nkb * G};
+    // Key blocks average half of the longest or more, so the rule never splits 384 of them.
+    if (whole.groups >= kKvSlots) return whole;
+    constexpr int share = kKvCus * 3 / 4;
+    for (int chunk = std::max(4, (int)((blocks * G + share - 1) / share)); chunk < kv_blocks(0, Sp, r); ++chunk) {
+        int n = 0;
+        for (int kb = 0; kb < nkb; ++kb) n += (kv_blocks(kb, Sp, r) + chunk - 1) / chunk;
+        if (n * G <= kKvSlots) return {chunk, n * G};   // the first one, but for uneven remainders
+    }
+    return whole;
 }
 
 }  // namespace
