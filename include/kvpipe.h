@@ -288,7 +288,9 @@ int kvp_set_kv_slot(kvp_ctx* ctx, int l, void* K, void* V);
  * for KVP_PHASE_BACKWARD the gradients in flight, (bf16 models) their
  * transposed copies and transposed weights and the partial sums of weight
  * gradients or of dK/dV that several workgroups share, (fp32 models) the per-(token,
- * head) softmax statistics, and the producers' fp32 dK/dV sums.
+ * head) softmax statistics, and the producers' fp32 dK/dV sums.  The size never
+ * shrinks as B or S grows: a workspace sized for max_batch and max_seq serves
+ * every call of its phase.
  * Errors: KVP_E_INVALID_ARG, KVP_E_CAPACITY (B > max_batch, S > max_seq).
  */
 int kvp_workspace_size(const kvp_ctx* ctx, int phase, int B, int S, size_t* bytes);

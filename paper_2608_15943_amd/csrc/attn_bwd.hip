@@ -869,8 +869,15 @@ KvPlan kv_plan(int B, int S, int a, int g) {
 }  // namespace
 
 size_t bwd_kv_part_floats(int B, int S, int a, int g) {
-    const KvPlan p = kv_plan(B, S, a, g);
-    return p.chunk ? p.groups * kKvSlot : 0;
+    const int Sp = (S + 63) / 64 * 64, r = a / g, nkb = (S + KV_BK - 1) / KV_BK;
+    const int64_t G = (int64_t)B * g;
+    // A split gives at most one workgroup per 4 blocks and one more per key block.
+    int64_t n = nkb * G, blocks = 0;
+    for (int kb = 0; kb < nkb && n < kKvSlots; ++kb) {
+        blocks += kv_blocks(kb, Sp, r);
+        n = nkb * G + (blocks * G + 3) / 4;
+    }
+    return (size_t)std::min<int64_t>(n, kKvSlots) * kKvSlot;
 }
 
 hipError_t transpose_bf16(Transposes t, hipStream_t st) {
@@ -925,7 +932,8 @@ hipError_t flash_bwd_kv_bf16(const AttnBwdKv& p, hipStream_t st) {
     const KvPlan plan = kv_plan(p.B, p.S, p.a, p.g);
     A.chunk = plan.chunk;
     A.part = p.part;
-    if (plan.chunk && !p.part) return hipErrorInvalidValue;
+    if (plan.chunk && (!p.part || plan.groups * kKvSlot > bwd_kv_part_floats(p.B, p.S, p.a, p.g)))
+        return hipErrorInvalidValue;
     if (plan.chunk) {
         hipLaunchKernelGGL(flash_bwd_kv_kernel<true>, dim3(plan.groups), dim3(KV_NT), 0, st, A);
         hipLaunchKernelGGL(kv_reduce_kernel, dim3((p.S + 31) / 32 * p.B * p.g), dim3(256), 0, st, A);

@@ -581,10 +581,10 @@ hipError_t gemm_out_f32(const uint16_t* a, const uint16_t* w, int M, int N, int 
 
 // Splitting K adds workgroups and shortens their chain, and pays for the fp32 planes: written,
 // read again and summed by a kernel of its own (about 5 us and 4.5 TB/s).
-int gemm_out_splits(int M, int N, int K) {
+int gemm_out_splits(int M, int N, int K, size_t part_floats) {
     int best = 1;
     float t = pick_tile(M, N, K, 1).us;
-    for (int s = 2; s <= 8 && s <= K / BK; s *= 2) {
+    for (int s = 2; s <= 8 && s <= K / BK && (size_t)s * M * N <= part_floats; s *= 2) {
         const float u = pick_tile(M, N, K, s).us + 5.f + (float)(s + 1) * (float)M * (float)N * 4.f / 4.5e6f;
         if (u < t) {
             t = u;

@@ -65,8 +65,9 @@ hipError_t gemm_out_bf16(const uint16_t* a, const uint16_t* w, int M, int N, int
 // slice s (sum them with reduce_planes).
 hipError_t gemm_out_f32(const uint16_t* a, const uint16_t* w, int M, int N, int K, int splits, float* part, float* dst0,
                         int rows0, float* dst1, int rows1, float* dst2, hipStream_t st);
-// The slice count gemm_out_f32 should use for an M x N x K product.
-int gemm_out_splits(int M, int N, int K);
+// The slice count gemm_out_f32 should use for an M x N x K product, its planes at most
+// part_floats.
+int gemm_out_splits(int M, int N, int K, size_t part_floats);
 
 // ---- bf16 backward ----------------------------------------------------------
 
@@ -111,8 +112,9 @@ struct AttnBwdKv {
     uint16_t* out_t;        // nullable: the same rows token-major, [ldo][B*S] (S % 8 == 0)
     int ldo, col_k, col_v;
     int B, S, Sp, a, g, cap;
-    float* part;            // bwd_kv_part_floats() of scratch (null when that is 0)
+    float* part;            // bwd_kv_part_floats() of scratch
 };
+// Never shrinks as B or S grows.
 size_t bwd_kv_part_floats(int B, int S, int a, int g);
 hipError_t flash_bwd_kv_bf16(const AttnBwdKv& p, hipStream_t st);
 

@@ -654,10 +654,12 @@ Saved saved_layout(const kvp_ctx& c, int B, int S) {
     return v;
 }
 
-// Workspace of kvp_backward.
+// Workspace of kvp_backward.  Every part, and so the whole, never shrinks as B or S grows: one
+// that holds a model's largest call holds all of its calls.
 struct BwdWs {
     size_t gb = 0, dO = 0, lse = 0, dsum = 0, dqkv = 0, acc = 0, wot = 0, wst = 0, part = 0, rope = 0, ta = 0, tb = 0,
-           tc = 0, total = 0;
+           total = 0;
+    size_t part_floats = 0;
     size_t acc_plane = 0;          // floats of one dK or dV sum
     std::vector<int> acc_slot;     // per layer: index of its fp32 sum pair, or -1
 };
@@ -697,26 +699,27 @@ BwdWs bwd_layout(const kvp_ctx& c, int B, int S) {
     w.gb = take(M * h * 2);
     w.dO = take(M * nq * 2);
     w.dsum = take((size_t)B * c.d.a * round64(S) * sizeof(float));
-    w.dqkv = take(M * np * 2);
+    const size_t Mp = (M + 63) / 64 * 64;
+    // Until the attention writes it, O^T (unless the forward saved it): [a*d_h][Mp].
+    w.dqkv = take(Mp * np * 2);
     w.acc = take((size_t)nacc * 2 * w.acc_plane * sizeof(float));
     w.wot = take(nq * h * 2);   // W_O^T [a*d_h][h]
     w.wst = take(h * np * 2);   // [W_Q; W_K; W_V]^T [h][np]
-    // Scratch of one step at a time: split-K planes of the weight-gradient GEMMs (consumers: Q
-    // rows only), or the chunk sums of dK, dV.
-    const size_t Mp = (M + 63) / 64 * 64;
+    // Scratch of one step at a time: the chunk sums of dK, dV, or split-K planes of the
+    // weight-gradient GEMMs (consumers: Q rows only).  The room for planes is what the slices
+    // of very many tokens take, but little more than one operand's copy (slices do not pay
+    // before that): it grows with the tokens, where the number of slices may not.
     auto planes = [&](size_t m, size_t n) {
-        const int sp = kvp::gemm_out_splits((int)m, (int)n, (int)Mp);
-        return sp > 1 ? sp * m * n : (size_t)0;
+        const int s = kvp::gemm_out_splits((int)m, (int)n, 1 << 22, SIZE_MAX);
+        return s > 1 ? std::min(s * m * n, Mp * std::max(h, np) * 5 / 8) : (size_t)0;
     };
-    w.part = take(std::max({planes(h, nq), planes(np, h), planes(nq, h),
-                            kvp::bwd_kv_part_floats(B, S, c.d.a, c.d.g)}) *
-                  sizeof(float));
+    w.part_floats = std::max({planes(h, nq), planes(np, h), planes(nq, h),
+                              kvp::bwd_kv_part_floats(B, S, c.d.a, c.d.g)});
+    w.part = take(w.part_floats * sizeof(float));
     w.rope = take((size_t)S * 64 * sizeof(float2));
-    // Token-major operands of the weight-gradient GEMMs: G^T then [dQ|dK|dV]^T; X^T; O^T
-    // unless the forward saved it.
+    // Token-major operands of the weight-gradient GEMMs: G^T then [dQ|dK|dV]^T; X^T.
     w.ta = take(Mp * std::max(h, np) * 2);
     w.tb = take(Mp * h * 2);
-    if (!tokmajor_direct(B, S)) w.tc = take(Mp * nq * 2);
     w.total = off;
     return w;
 }
@@ -1145,7 +1148,7 @@ extern "C" int kvp_backward(kvp_ctx* ctx, const void* x, const void* dy, void* d
         const uint16_t* Xl = l == 0 ? (const uint16_t*)x : (const uint16_t*)(lay + sv.x);
 
         // The operands known so far, in one launch: W_O^T, [W_Q; W_K; W_V]^T, G^T, X^T (, O^T).
-        uint16_t *ta = bp(w.ta), *tb = bp(w.tb), *tc = bp(w.tc);
+        uint16_t *ta = bp(w.ta), *tb = bp(w.tb), *tc = dqkv;   // dqkv is free until the attention
         const uint16_t* Ot = sv.has_ot ? (const uint16_t*)(lay + sv.ot) : tc;
         if ((rc = aux([&] {
                  kvp::Transposes t;
@@ -1171,7 +1174,7 @@ extern "C" int kvp_backward(kvp_ctx* ctx, const void* x, const void* dy, void* d
         // C = a^T b over the tokens, rows to up to three gradient buffers.
         auto weight_grad = [&](const uint16_t* at, const uint16_t* bt, int rows, int cols, float* d0, int r0, float* d1,
                                int r1, float* d2, const char* what) {
-            const int s = kvp::gemm_out_splits(rows, cols, Mp);
+            const int s = kvp::gemm_out_splits(rows, cols, Mp, w.part_floats);
             int r2 = gemm([&] {
                 return check_hip(kvp::gemm_out_f32(at, bt, rows, cols, Mp, s, part, d0, r0, d1, r1, d2, st), what);
             });

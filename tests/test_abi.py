@@ -433,3 +433,27 @@ def test_noalloc_decode_rejects_workspace_beyond_the_static_array():
         m.kvp_decode_step_noalloc(fake, fake * 2, 10, fake * 4, 0)
     assert e.value.code == kb.KVP_E_INVALID_ARG
     assert kb.lib().kvp_decode_step_noalloc(None, fake, fake, 1, fake, 1, None) == kb.KVP_E_INVALID_ARG
+
+
+@pytest.mark.parametrize("h,a,g,tau", [
+    (256, 2, 1, [0, 0]), (1024, 8, 4, [0, 1, 1]), (2048, 16, 8, [0, 0]), (2048, 16, 16, [0, 1]),
+    (4096, 32, 8, [0, 0]), (5120, 40, 8, [0]), (8192, 64, 8, [0, 0]),
+])
+def test_workspace_sizes_never_shrink(h, a, g, tau):
+    """A workspace sized for the largest batch and length serves every smaller call, in each
+    phase: sizes do not shrink as B or S grows (odd lengths, lengths around multiples of 8, 64
+    and 256, token counts around multiples of 512 and of the chunked and split launches)."""
+    m = kb.Model(len(tau), h, a, g, 128, kb.KVP_DTYPE_BF16, tau, max_batch=64, max_seq=16384, kv_capacity=16384)
+    S = sorted({s + e for s in list(range(64, 2049, 64)) + [2560, 3000, 4096, 5120, 8192, 12288, 16384]
+                for e in (-8, -1, 0) } | {1, 7, 8, 9, 100, 777})
+    Bs = list(range(1, 34)) + [40, 48, 63, 64]
+    for phase in (kb.KVP_PHASE_PREFILL, kb.KVP_PHASE_BACKWARD):
+        last = [0] * len(S)
+        for B in Bs:
+            row = [m.kvp_workspace_size(phase, B, s) for s in S]
+            assert row == sorted(row), (phase, B, [s for s, x, y in zip(S, row, row[1:]) if y < x])
+            assert all(x <= y for x, y in zip(last, row)), (phase, B)
+            last = row
+    sizes = [m.kvp_workspace_size(kb.KVP_PHASE_DECODE, B) for B in Bs]
+    assert sizes == sorted(sizes)
+    m.close()
