@@ -33,7 +33,8 @@ __device__ __forceinline__ float softmax_step(float (&s)[4], float& m, float& l)
     float t = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        s[e] = mn == -INFINITY ? 0.f : expf(s[e] - mn);
+        // By the score, not by the maximum, which passes over NaN: a NaN score stays one.
+        s[e] = s[e] == -INFINITY ? 0.f : expf(s[e] - mn);
         t += s[e];
     }
     l = l * a + quad_sum(t);
