@@ -19,6 +19,11 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// Start of a running maximum of scaled scores (log2 domain): finite, so that keys whose scores
+// are -inf weigh exp2(-inf) = 0 before and after the first finite one, and below every finite
+// score (those end at FLT_MAX * log2(e) / sqrt(128) = 4.4e37).
+constexpr float kNoScore = -1e38f;
+
 constexpr int kWave = 64;
 constexpr int kNumXcd = 8;  // MI355X: 8 XCDs, workgroups are dealt to them round-robin
 

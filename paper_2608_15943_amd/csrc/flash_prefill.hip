@@ -261,7 +261,7 @@ __global__ __launch_bounds__(512, 2) void flash_prefill_kernel(
     f32x16 o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = f32x16{};
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = kNoScore, l_run = 0.f;
 
     const int ksw = swap_b23(l32);          // K row read by this lane inside a 32-row block
     // LDS byte addresses of this lane's fragments in stage 0: K step ks of block 0 (block mb is
@@ -382,8 +382,6 @@ __global__ __launch_bounds__(512, 2) void flash_prefill_kernel(
 #pragma unroll
                 for (int db = 0; db < 4; ++db) o[db] *= alpha;
             }
-            // The second half's first scores may all be -inf: their weights are 0, not NaN.
-            const float m_sub = KS == 2 && kw && m_run == -INFINITY ? 0.f : m_run;
             bf16x8 pb[KB][2];
 #pragma unroll
             for (int mb = 0; mb < KB; ++mb)
@@ -392,7 +390,7 @@ __global__ __launch_bounds__(512, 2) void flash_prefill_kernel(
                     float e[8];
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
-                        e[k] = __builtin_amdgcn_exp2f(fmaf(s[mb][8 * p + k], scale_log2, -m_sub));
+                        e[k] = __builtin_amdgcn_exp2f(fmaf(s[mb][8 * p + k], scale_log2, -m_run));
                         l_run += e[k];
                     }
                     u32x4 w;

@@ -1,4 +1,6 @@
-"""Scores that are not finite: a NaN key reaches every query that sees it and no other."""
+"""Scores that are not finite.  A NaN key reaches every query that sees it and no other; keys
+whose scores are -inf (a product past the fp32 range) weigh nothing, wherever they lie in the
+runs of keys that the attention kernels sum separately."""
 import math
 
 import numpy as np
@@ -73,3 +75,61 @@ def test_fp32_nan_key_reaches_the_gradients():
                           st)
     torch.cuda.synchronize()
     assert torch.isnan(dx).all()
+
+
+def _hidden_reference(x, wq, K, V, hidden, heads, S):
+    """Attention of x over K, V [S][128] without the hidden keys, in 64 bits; rows that see no
+    other key are NaN."""
+    d = 128
+    ang = np.arange(S)[:, None] * 10000.0 ** (-2.0 * np.arange(d // 2) / d)[None]
+    out = []
+    for j in range(heads):
+        q = x @ wq[j * d:(j + 1) * d].T
+        a, b = q[:, : d // 2], q[:, d // 2:]
+        q = np.concatenate([a * np.cos(ang) - b * np.sin(ang), b * np.cos(ang) + a * np.sin(ang)], 1)
+        s = q @ K.T / math.sqrt(d)
+        see = np.tril(np.ones((S, S), bool)) & ~hidden[None]
+        s = np.where(see, s, -np.inf)
+        with np.errstate(invalid="ignore"):
+            p = np.exp(s - s.max(1, keepdims=True))
+            out.append(p @ V / p.sum(1, keepdims=True))
+    return np.concatenate(out, 1)
+
+
+@pytest.mark.parametrize("lo,hi", [(0, 64), (64, 128), (0, 128), (128, 192)])
+@pytest.mark.parametrize("B", [1, 200])
+def test_flash_keys_with_scores_of_minus_infinity(lo, hi, B):
+    """Keys [lo, hi) score -inf for every query.  B 1 splits the keys of a tile between wave
+    groups, so a group's first 64 keys can all be such; B 200 does not."""
+    S, a = 260, 2
+    w = small_workload("inf-keys", 2, a * 128, a, 1, [0, 0], seed=47)
+    say(f"[-inf keys] {lo}..{hi} B={B}")
+    dm = build_device_model(w, B, S, 320, fill_cache_npos=S)
+    # Dimension 63 of every query is about 8 (it turns by 1.2e-4 a position), and of the hidden
+    # keys -3e38: the product leaves the fp32 range.
+    wq = dm.tensors["wq1"]
+    for j in range(a):
+        wq[128 * j + 63] = 0
+        wq[128 * j + 63, 0] = 8
+        wq[128 * j + 127] = 0
+    x = torch.from_numpy(np.ascontiguousarray(ki.prefill_x(w, [0], np.arange(S)))).to(tdtype(w))
+    x[:, :, 0] = 1
+    x = x.expand(B, S, w.h).contiguous().to(DEV)
+    K, V = dm.slots[0]
+    K.copy_(K[:1].expand_as(K).clone())
+    V.copy_(V[:1].expand_as(V).clone())
+    K[:, :, :, 63] = 0
+    K[:, :, lo:hi, 63] = -3e38
+    o, _ = _consumer(dm, x, B, S)
+    hidden = np.zeros(S, bool)
+    hidden[lo:hi] = True
+    k64 = to_np(K[0, 0, :S])
+    k64[hidden] = 0
+    ref = _hidden_reference(to_np(x[0]), to_np(wq), k64, to_np(V[0, 0, :, :S]).T, hidden, a, S)
+    for b in {0, B - 1}:
+        got = to_np(o[b])
+        none = np.isnan(ref).any(1)                     # rows that see hidden keys only
+        assert none.sum() == (hi if lo == 0 else 0)
+        assert np.isnan(got[none]).all()
+        err = np.abs(got[~none] - ref[~none]).max()
+        assert err <= 2e-2 * np.abs(ref[~none]).max(), err
