@@ -159,7 +159,7 @@ __global__ __launch_bounds__(64, 1) void decode_attn_kernel(
     f32x4 o[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = f32x4{};
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = kNoScore, l_run = 0.f;
 
     DTile cur, nxt;
     load(b, kvh, TILE * t, cur);
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(64, 1) void decode_attn_kernel(
             if (more) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) o[i] = f32x4{};
-                m_run = -INFINITY;
+                m_run = kNoScore;
                 l_run = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) qf[ks] = qn[ks];

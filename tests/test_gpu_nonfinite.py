@@ -133,3 +133,34 @@ def test_flash_keys_with_scores_of_minus_infinity(lo, hi, B):
         assert np.isnan(got[none]).all()
         err = np.abs(got[~none] - ref[~none]).max()
         assert err <= 2e-2 * np.abs(ref[~none]).max(), err
+
+
+@pytest.mark.parametrize("tiles", [(0,), (1,), (1, 2, 700)])
+def test_decode_tiles_with_scores_of_minus_infinity(tiles):
+    """A context of 1500 tiles of 64 positions over 1024 waves: some waves have one tile, some
+    two, so hidden tiles start, end and fill the pieces."""
+    n = 1500 * 64 - 1
+    w = small_workload("inf-decode", 1, 128, 1, 1, [0], seed=53)
+    say(f"[-inf decode] {tiles}")
+    dm = build_device_model(w, 1, 1, 1500 * 64, fill_cache_npos=n)
+    x = torch.from_numpy(np.ascontiguousarray(ki.decode_x(w, [0]))).to(tdtype(w)).to(DEV)
+    x64, wq = to_np(x[0]), to_np(dm.tensors["wq0"])
+    q = wq @ x64
+    ang = n * 10000.0 ** (-2.0 * np.arange(64) / 128)
+    q = np.concatenate([q[:64] * np.cos(ang) - q[64:] * np.sin(ang), q[64:] * np.cos(ang) + q[:64] * np.sin(ang)])
+    assert np.abs(q).sum() > 8                          # times 3e38: past the fp32 range
+    K, V = dm.slots[0]
+    hidden = np.zeros(n + 1, bool)
+    for t in tiles:
+        hidden[64 * t:64 * t + 64] = True
+        K[0, 0, 64 * t:64 * t + 64] = torch.from_numpy(-3e38 * np.sign(q)).to(K)
+    y = torch.zeros_like(x)
+    ws, nb = workspace(dm, kb.KVP_PHASE_DECODE, 1)
+    lens = torch.tensor([n], dtype=torch.int32, device=DEV)
+    dm.model.kvp_decode_step(x.data_ptr(), lens.data_ptr(), n, y.data_ptr(), 1, ws.data_ptr(), nb,
+                             torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    s = to_np(K[0, 0])[~hidden] @ q / math.sqrt(128)
+    p = np.exp(s - s.max())
+    ref = x64 + to_np(dm.tensors["wo0"]) @ ((p / p.sum()) @ to_np(V[0, 0]).T[~hidden])
+    assert np.abs(to_np(y[0]) - ref).max() <= 2e-2 * np.abs(ref).max()
