@@ -125,6 +125,26 @@ def small_workload(name, L, h, a, g, tau, dtype="bf16", d_h=128, seed=0):
                        phase="prefill", batch=1, seq=1, seed=seed)
 
 
+def attention_reference(x, lw: oat.LayerWeights, K, V, a: int, base: float, drop=()):
+    """Attention output [S, a * 128] of a bf16 layer on x [S, h] over the K, V [g, S, 128] that the
+    device holds, and a bound on the device's difference from it, element by element.
+
+    Q is rounded to bf16 as on the device.  Left are the roundings of the weights P and of the
+    output to bf16 (8 bits: 2^-9 of each), so 2^-9 (sum_j P_j |V_j| + |o|); twice that, for the
+    fp32 sums and the elements of Q whose rounding falls the other way.  ``drop``: keys left out
+    of the output (a planted mistake, for the test of the bound)."""
+    pos = np.arange(x.shape[0])
+    kpos = pos.copy()
+    kpos[list(drop)] = x.shape[0]        # past every query
+    q, _, _ = oat.project_qkv(np.asarray(x, dtype=np.float64), pos, lw, a, K.shape[0], K.shape[2], base, kv=False)
+    q = ki.round_to_bf16(q.astype(np.float32)).astype(np.float64)
+
+    def rows(v, kp):
+        return oat.attention(q, K, v, pos, kp).transpose(1, 0, 2).reshape(x.shape[0], -1)
+
+    return rows(V, kpos), 2.0**-8 * (rows(np.abs(V), pos) + np.abs(rows(V, pos)))
+
+
 def _align256(n: int) -> int:
     return (n + 255) // 256 * 256
 

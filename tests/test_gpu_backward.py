@@ -127,6 +127,11 @@ def _train_case(w, B, S, cap):
     (512, 4, 1, [0, 0], 2, 531),
     (256, 2, 2, [0, 1], 1, 1090),
     (512, 4, 1, [0, 0, 0], 1, 512),
+    # 1554 tokens (padded to 1600) at width 2048: dO, dW_O, the consumer's dW_Q and both dX on
+    # 128 x 128 tiles, [dW_Q; dW_K; dW_V] to its three buffers on 128 x 256.
+    (2048, 16, 8, [0, 0], 2, 777),
+    # 2600 tokens: dO and dX on 128 x 256 tiles.
+    (2048, 16, 8, [0, 0], 2, 1300),
 ])
 def test_backward_matches_oracle(h, a, g, tau, B, S):
     w = small_workload(f"bwd-h{h}-a{a}-g{g}", len(tau), h, a, g, tau, seed=21)
