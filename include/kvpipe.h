@@ -54,6 +54,12 @@
  *   fp32 (workspace), with a bf16 copy as the next projection's operand; the
  *   caller's x and y are bf16.  fp32 models run every step in fp32 on the
  *   vector units (no reduced-precision modes).
+ * - Equal calls give equal bits.  How long sums are split over workgroups follows
+ *   the sizes of the whole call: the keys of a bf16 prefill's attention by B, S
+ *   and a, the positions of a decode step by every sequence's length, the
+ *   queries and tokens of the backward by B and S.  A sequence's results may
+ *   therefore differ in their last bits between a call alone and a call in a
+ *   batch, or between lengths; each is within the roundings stated above.
  */
 #ifndef KVPIPE_H
 #define KVPIPE_H

@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256) void attn_bwd_prep_kernel(const uint16_t* __re
 //   dP [32 q x 32 k] = dO V^T    (A = dO rows, same order; B = V^T tile along its rows)
 //   dV [32 k x 128]  += P^T dO   (A = P from the S registers; B = dO tile along its rows)
 //   dK [32 k x 128]  += dS^T Q   (A = dS; B = Q tile along its rows)
-// The operands taken along a tile's rows are transposed reads (tr_frag), so no transposed
+// The operands taken along a tile's rows are transposed fragments (lds_tr.h), so no transposed
 // copy of Q, dO or V is made.
 // ---------------------------------------------------------------------------
 struct KvArgs {
@@ -333,12 +333,11 @@ __global__ __launch_bounds__(KV_NT, 2) void flash_bwd_kv_kernel(KvArgs A) {
         dv[i] = f32x16{};
     }
     const int rsw = swap_b23(l32);
-    // The transposed-read lane offsets of tr_frag<KV_BQ, false> (row r0 = 0, column block 0):
-    // the rest of a fragment's address is an immediate.
+    // The lane offsets of a transposed fragment (0, 0): the rest of an address is an immediate.
     const int tr_row = 8 * (lane >> 5) + ((lane & 15) >> 2), tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
     const int tr_lo = sub_off<KV_BQ>(tr_row, tr_col), tr_up = sub_off<KV_BQ>(tr_row + 4, tr_col);
-    // Row chunks of row8<KV_BQ>(tile, rsw, 16 ks + 8 hi) for even and odd ks (block 0, rows
-    // 0..31), and the V^T fragment of tr_frag<D, false>(lvt, 16 ks, 32 wave) at ks = 0.
+    // Row fragments (row rsw, columns 16 ks + 8 hi) for even and odd ks (block 0, rows 0..31),
+    // and the transposed fragment (16 ks, 32 wave) of V^T at ks = 0.
     const int rc0 = sub_off<KV_BQ>(rsw, 8 * hi), rc1 = sub_off<KV_BQ>(rsw, 16 + 8 * hi);
     const uint32_t av_lo = (uint32_t)(uintptr_t)((const char*)lvt + wave * (D * 64) + sub_off<D>(tr_row, tr_col)),
                    av_up = (uint32_t)(uintptr_t)((const char*)lvt + wave * (D * 64) + sub_off<D>(tr_row + 4, tr_col));
@@ -693,10 +692,10 @@ __global__ __launch_bounds__(Q_NT, 2) void flash_bwd_q_kernel(QArgs A) {
     const int rsw = swap_b23(l32);
 
     // Per-lane LDS addresses in stage 0 (stage 1 is a constant offset further: the loop below
-    // takes the stage as a compile-time constant).  K row chunk of row8<Q_BKV>(lk, rsw,
-    // 16 ks + 8 hi) for even and odd ks; the two transposed reads of tr_frag<D, true>(lvt, 0, 0)
-    // and of tr_frag<Q_BKV, false>(lk, 0, 0).  Row blocks, column blocks, k steps and the
-    // stage are immediates.
+    // takes the stage as a compile-time constant).  K's row fragment (row rsw, columns
+    // 16 ks + 8 hi) for even and odd ks; the two reads of the permuted transposed fragment (0, 0)
+    // of V^T and of the plain one of K.  Row blocks, column blocks, k steps and the stage are
+    // immediates.
     const int G = lane >> 4, a4 = lane & 3;
     const int tr_row = 8 * (G >> 1) + ((lane & 15) >> 2);
     const int tr_col = 16 * (G & 1) + 4 * a4, trp_col = 16 * (G & 1) + 4 * (((a4 & 1) << 1) | (a4 >> 1));

@@ -13,7 +13,7 @@
 // 128 x 128) had nothing to run while it waited for its fragments and for the tile behind
 // the barrier.  Operands go from global memory straight into LDS, two stages of 64 KB; each
 // part of a stage is requested again as soon as its fragments are in registers, so a load
-// has two slots pairs (a whole K step of the workgroup) before its wait, which leaves the
+// has two pairs of slots (a whole K step of the workgroup) before its wait, which leaves the
 // newer loads in flight.
 //
 // gemm_half (128 x 256, the same turns) and gemm_small (128 x 128, 64 x 64 per workgroup of 4
@@ -37,7 +37,6 @@ constexpr int BM = 256, BN = 256, BK = 64, GROUP_M = 8;
 // Word 3 of a raw buffer resource: a valid (32-bit) data format.
 constexpr int kRsrcWord3 = 0x00020000;
 
-typedef __attribute__((address_space(1))) void gvoid_t;
 typedef __attribute__((address_space(3))) void lvoid_t;
 
 // LDS position of 16-byte chunk c of tile row r (rows are 128 B): spreads 16 consecutive
@@ -164,8 +163,8 @@ constexpr int kBigNT = 512;
 // 128..255) and B0, B1 (columns likewise) of tile kt + 2 are requested into stage kt % 2 once
 // both groups have read tile kt's (A0, B0, B1: in phase b of tile kt; A1: in phase a of tile
 // kt + 1), 16 KB each, two loads per wave.  Every read slot ends with a wait for the parts
-// the next phase reads; at most the 8 newer loads stay in flight.  MODE 1 and 2 are the last
-// two tiles: nothing (but A1) left to request, so the waits count down.
+// the next phase reads; the 8 newer loads stay in flight, also at the end, where tiles past
+// the last one are requested beyond their resource.
 template <class Epi>
 __global__ __launch_bounds__(kBigNT, 2) void gemm_big(const uint16_t* __restrict__ A, WRows W, int M, int N, int K,
                                                      int splits, Epi epi) {

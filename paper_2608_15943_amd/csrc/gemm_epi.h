@@ -1,8 +1,9 @@
 // Epilogues of the bf16 GEMMs (gemm_bf16.hip).  A workgroup's fp32 accumulators go through
-// LDS: a pass stages ROWS rows of the tile's BN columns (stage()), then all NT threads copy
+// LDS: a pass stages ROWS rows of the tile's BN columns (st_block()), then all NT threads copy
 // the pass out with coalesced 16-byte global accesses (flush()), applying the fused work.
-// The global inputs of a pass (cos/sin rows, residual) are requested by prefetch() before
-// the staging, so that their latency runs under the LDS writes and the barrier.
+// The global inputs of a pass (cos/sin rows, residual) are requested by prefetch(): before
+// the staging in gemm_small, so that their latency runs under the LDS writes and the
+// barrier; after it in the 8-wave kernels, in the registers that the staging has freed.
 //
 // Staged layout: row m is BN floats; its 16-byte chunk c sits at position
 // c ^ ((m / 8) % 16) ^ (8 if m & 4).  An accumulator lane pair (l, l + 32) writes 128
