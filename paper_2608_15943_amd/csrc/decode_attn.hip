@@ -26,6 +26,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -291,7 +293,10 @@ __global__ __launch_bounds__(64, 1) void decode_attn_kernel(
 // before the four waves' results meet in LDS.  The kernel is a few dependent load latencies
 // and the fetch of its own code; weights in LDS for the whole workgroup, with three barriers,
 // or the values requested early by unrolled code were 0.8 us longer at one sequence of 977
-// positions (4.4 and 5.2 us).
+// positions (4.4 and 5.2 us).  The values of 8 and then of 4 pieces are requested at once: one
+// piece after the other took (step of two layers, 16/1 heads, one sequence of 120 000: 1024
+// pieces) 204 us, this 81; 64/8 heads, 8000: 162 and 152; batches of 4 alone 97 and 152, of 16
+// 72 and 155 (their remainder goes one by one).
 __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
     const float* __restrict__ part, const int32_t* __restrict__ lens, uint16_t* __restrict__ O, int B,
     int a, int g, int cap, int W) {
@@ -322,12 +327,22 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
         den = den * f + wave_sum(wt * l);
         num *= f;
         M = Mn;
-        for (int s = 0; s < c; ++s) {
-            const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wt), s));
-            const f32x2 x = *(const f32x2*)(pr + s * step + 2 * lane);
-            num[0] += w * x[0];
-            num[1] += w * x[1];
-        }
+        auto add = [&](auto n_t, int s) __attribute__((always_inline)) {
+            constexpr int n = decltype(n_t)::value;
+            f32x2 x[n];
+#pragma unroll
+            for (int i = 0; i < n; ++i) x[i] = *(const f32x2*)(pr + (s + i) * step + 2 * lane);
+#pragma unroll
+            for (int i = 0; i < n; ++i) {
+                const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wt), s + i));
+                num[0] += w * x[i][0];
+                num[1] += w * x[i][1];
+            }
+        };
+        int s = 0;
+        for (; s + 8 <= c; s += 8) add(std::integral_constant<int, 8>{}, s);
+        for (; s + 4 <= c; s += 4) add(std::integral_constant<int, 4>{}, s);
+        for (; s < c; ++s) add(std::integral_constant<int, 1>{}, s);
     }
     *(f32x2*)&num_s[wave][2 * lane] = num;
     if (lane == 0) {

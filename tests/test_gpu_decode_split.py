@@ -27,6 +27,9 @@ def _gpu():
     (4, 1, [64] * 15 + [65]),           # T = 1025
     (4, 2, [64] * 15 + [65]),           # T = 2050
     (4, 1, [1, 200, 1, 3, 820]),        # T = 1025, ranges that cross several sequences
+    # Fewer tiles than waves, so as many pieces as tiles to merge, four waves in turn: up to 1,
+    # 3 and 4, 5, 7 and 8, 9, 12, 13 and 16 pieces a wave.
+    (4, 1, [4, 15, 17, 31, 33, 48, 49, 63]),
 ])
 def test_tiles_around_the_number_of_waves(a, g, tiles):
     w = small_workload(f"split-a{a}-g{g}-{sum(tiles)}", 2, a * 128, a, g, [0, 0], seed=31)
