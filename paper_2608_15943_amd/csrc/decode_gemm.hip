@@ -278,23 +278,32 @@ __device__ __forceinline__ const uint16_t* w_row3(const WRows& w, int n, int K) 
     return (const uint16_t*)w.p[2] + (size_t)n * K;
 }
 
-// MODE 0, with at most one workgroup per CU and fewer than 16 slices: one wave more than K has
-// slices computes the workgroup's cos / sin in double while the others wait for their weights
-// (4096 columns of K = 4096, one row: 8.9 -> 8.0 us).  A CU with several workgroups hides them
-// anyway, and the larger workgroup costs it more (6144 columns, 8 rows: +0.5 us).  Between the
-// waves' own loads and products they spilled the loads (14 -> 36 us).
-template <int MODE>   // 0: projections with RoPE + cache append, 1: output projection + residual
+// MODE 0: projections with RoPE + cache append, 1: output projection + residual.
+// Cosines and sines of MODE 0 (in double), by CS, chosen at the launch:
+//   2  by one wave more than K has slices while the others wait for their weights: at most one
+//      workgroup per CU and fewer than 16 slices (4096 columns of K = 4096, one row: 8.9 ->
+//      8.0 us).  A CU with several workgroups hides them anyway, and the larger workgroup costs
+//      it more (6144 columns, 8 rows: +0.5 us).
+//   1  by the waves themselves ahead of the barrier.
+//   0  behind it, by the threads that use them: the compiler keeps more of the weight loads in
+//      flight, which matters to workgroups of many waves (one or two to a CU).  Two layers'
+//      average, us, 1 / 0: K 8192, 64/16 heads, 12 rows 48.1 / 44.9; K 7168, 16 rows 44.2 /
+//      41.8; K 6144, 8 rows 27.7 / 26.5; K 5120, 8 rows 20.1 / 20.9, 16 rows 26.2 / 25.1;
+//      K 4096, 4 rows 13.3 / 14.0.
+// Between the waves' own loads and products they spilled the loads (14 -> 36 us).
+template <int MODE, int CS>   // MODE 0: projections with RoPE + cache append, 1: output projection + residual
 __global__ __launch_bounds__(1024) void gemm_decode_fused_kernel(const uint16_t* __restrict__ X, WRows W, int M,
                                                                  int N, int K, FusedQkv fq, FusedResid fr) {
     constexpr int D = 128, HALF = 64;
     __shared__ float red[16][16 * 16];   // [wave][row * 16 + column]
-    __shared__ float2 cs_s[MODE == 0 ? 16 * 8 : 1];   // [row][rotary pair of the workgroup]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = K / 512;
+    __shared__ float2 cs_s[CS ? 16 * 8 : 1];   // [row][rotary pair of the workgroup]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6,
+              nw = CS == 2 ? K / 512 : blockDim.x >> 6;
     const int col = lane & 15, kg = lane >> 4;
     const int j = blockIdx.x;
     const int nrot = MODE == 0 ? (fq.a + (fq.producer ? fq.g : 0)) * D : 0;   // rotary columns
     const bool rot = 16 * j < nrot;
-    if (wave < nw) {
+    if (CS != 2 || wave < nw) {
         const int n = rot ? (j >> 3) * D + (col < 8 ? 0 : HALF) + (j & 7) * 8 + (col & 7) : 16 * j + col;
         const int k0 = 512 * wave;
         const uint16_t* wr = w_row3(W, n, K) + k0 + 8 * kg;
@@ -312,10 +321,9 @@ __global__ __launch_bounds__(1024) void gemm_decode_fused_kernel(const uint16_t*
 #pragma unroll
         for (int i = 0; i < 4; ++i) red[wave][(4 * kg + i) * 16 + col] = acc[i];
     }
-    if constexpr (MODE == 0) {
-        const bool extra = blockDim.x > 64 * (unsigned)nw;
-        if (rot && (wave == nw || !extra))
-            for (int t = extra ? lane : threadIdx.x; t < 8 * M; t += extra ? 64 : blockDim.x) {
+    if constexpr (CS != 0) {
+        if (rot && (wave == nw || CS == 1))
+            for (int t = CS == 2 ? lane : threadIdx.x; t < 8 * M; t += CS == 2 ? 64 : blockDim.x) {
                 const int pos = max(0, min(fq.lens[t >> 3], fq.cap - 1));
                 const double theta = pow(fq.base, -2.0 * ((j & 7) * 8 + (t & 7)) / D);
                 double sd, cd;
@@ -362,7 +370,17 @@ __global__ __launch_bounds__(1024) void gemm_decode_fused_kernel(const uint16_t*
                 const int row = t >> 3, c = t & 7;
                 const int h = j >> 3, i = (j & 7) * 8 + c;
                 const int pos = max(0, min(fq.lens[row], fq.cap - 1));
-                const float cs = cs_s[t].x, sn = cs_s[t].y;
+                float cs, sn;
+                if constexpr (CS == 0) {
+                    const double theta = pow(fq.base, -2.0 * i / D);
+                    double sd, cd;
+                    sincos((double)pos * theta, &sd, &cd);
+                    cs = (float)cd;
+                    sn = (float)sd;
+                } else {
+                    cs = cs_s[t].x;
+                    sn = cs_s[t].y;
+                }
                 const float x1 = sum(row, c), x2 = sum(row, c + 8);
                 const float o1 = x1 * cs - x2 * sn, o2 = x2 * cs + x1 * sn;
                 if (h < fq.a) {
@@ -405,8 +423,15 @@ hipError_t gemm_decode_qkv_fused_bf16(const uint16_t* x, const WRows& w, int B, 
     FusedQkv fq{q, kc, vc, lens, a, g, cap, producer ? 1 : 0, base, pages};
     const int waves = K / 512;
     const bool extra = waves < 16 && N / 16 <= 256;
-    hipLaunchKernelGGL(gemm_decode_fused_kernel<0>, dim3(N / 16), dim3(64 * (waves + (extra ? 1 : 0))), 0, st, x, w, B,
-                       N, K, fq, FusedResid{});
+    if (extra)
+        hipLaunchKernelGGL((gemm_decode_fused_kernel<0, 2>), dim3(N / 16), dim3(64 * (waves + 1)), 0, st, x, w, B, N, K, fq,
+                           FusedResid{});
+    else if (waves <= 8 || (waves <= 11 && B <= 8))
+        hipLaunchKernelGGL((gemm_decode_fused_kernel<0, 1>), dim3(N / 16), dim3(64 * waves), 0, st, x, w, B, N, K, fq,
+                           FusedResid{});
+    else
+        hipLaunchKernelGGL((gemm_decode_fused_kernel<0, 0>), dim3(N / 16), dim3(64 * waves), 0, st, x, w, B, N, K, fq,
+                           FusedResid{});
     return hipGetLastError();
 }
 
@@ -414,7 +439,7 @@ hipError_t gemm_decode_resid_fused_bf16(const uint16_t* x, const WRows& w, int M
                                         bool x_f32, uint16_t* y, float* yf, hipStream_t st) {
     if (!decode_fused_ok(M, N, K)) return hipErrorInvalidValue;
     FusedResid fr{x_res, x_f32 ? 1 : 0, y, yf};
-    hipLaunchKernelGGL(gemm_decode_fused_kernel<1>, dim3(N / 16), dim3(64 * (K / 512)), 0, st, x, w, M, N, K,
+    hipLaunchKernelGGL((gemm_decode_fused_kernel<1, 0>), dim3(N / 16), dim3(64 * (K / 512)), 0, st, x, w, M, N, K,
                        FusedQkv{}, fr);
     return hipGetLastError();
 }
