@@ -9,7 +9,8 @@
 // T mod W of the waves), whatever the mix of lengths, and a range may run
 // from the end of one pair into the next without a pipeline bubble.  (With ranges of
 // ceil(T / W) tiles the last waves had none: 8 sequences of 4100 positions are 4.004
-// tiles a wave, 5 for four fifths of the waves, 26.7 us.)  Each piece
+// tiles a wave, 5 for four fifths of the waves, 26.7 us.)  Lists of up to 3 tiles a wave
+// run on fewer waves (Split).  Each piece
 // of a range that lies in one pair ends in a partial result (running max m, sum
 // l, unnormalised O); the piece of wave w in pair P goes to slot w + P, which is
 // unique because w and P never both decrease along the list.
@@ -60,13 +61,23 @@ __device__ __forceinline__ SeqTiles seq_tiles(const int32_t* lens, int B, int ca
     return t;
 }
 
-// The list's split over W = min(waves, T) waves: wave w starts at tile floor(w T / W)
+// The list's split over W waves: wave w starts at tile floor(w T / W)
 // (T < 2^31: 64 sequences of at most 2^17 tiles and at most 256 KV heads).  Waves with one
 // tile more than others are spread over the grid: starts at one power-of-two stride (64
 // sequences of 32K: 256 tiles) meet in the same memory channels, 0.7 % slower.
+// Up to 3 tiles a wave, no more waves run than it takes at ceil(T / waves) tiles each: the
+// longest range is the same, and up to 768 waves of a short range finish sooner than 1024
+// (32/8 heads, T / waves, us, all waves / as few as it takes: 1.06 15.1 / 13.2, 1.5 15.6 /
+// 13.9, 1.75 15.9 / 15.6, 2.06 20.1 / 16.6, 2.25 19.8 / 17.7, 2.75 20.3 / 20.1).  Beyond, all
+// waves: 3.06 23.7 / 24.1, 4.06 27.9 / 28.2, 6.06 35.9 / 36.9 (5.4, the other way, 34.3 / 33.3).
 struct Split {
     uint32_t T, W, q, rem;
-    __device__ __forceinline__ Split(uint32_t T_, uint32_t waves) : T(T_), W(min(waves, T_)), q(T_ / W), rem(T_ % W) {}
+    static __device__ __forceinline__ uint32_t waves_of(uint32_t T, uint32_t waves) {
+        if (T > 3 * waves) return waves;
+        const uint32_t c = T <= waves ? 1 : T <= 2 * waves ? 2 : 3;
+        return (T + c - 1) / c;
+    }
+    __device__ __forceinline__ Split(uint32_t T_, uint32_t waves) : T(T_), W(waves_of(T_, waves)), q(T_ / W), rem(T_ % W) {}
     __device__ __forceinline__ uint32_t start(uint32_t w) const { return w * q + w * rem / W; }   // w <= W <= 4096
     // The wave that holds tile x: ceil((x + 1) W / T) - 1.  The quotient is exact in double (an
     // integer below 2^43 over one below 2^31).

@@ -1,7 +1,7 @@
 """The decode attention deals its list of 64-position tiles over 1024 waves (256 CUs), or over
-one wave per tile when there are fewer.  One tile fewer, as many, one more than waves, and
-twice as many and one, with one and with two KV heads; and a single tile; against the fp64
-oracle at the bf16 tolerance."""
+as few waves as it takes at one, two or three tiles each.  One tile fewer, as many, one more than
+waves, and the same around twice and three times as many, with one and with two KV heads; and a
+single tile; against the fp64 oracle at the bf16 tolerance."""
 import pytest
 import torch
 
@@ -25,7 +25,11 @@ def _gpu():
     (4, 1, [64] * 15 + [63]),           # T = 1023
     (4, 1, [64] * 16),                  # T = 1024
     (4, 1, [64] * 15 + [65]),           # T = 1025
+    (4, 2, [64] * 16),                  # T = 2048
     (4, 2, [64] * 15 + [65]),           # T = 2050
+    (4, 2, [64] * 23 + [63]),           # T = 3070
+    (6, 3, [64] * 16),                  # T = 3072
+    (4, 1, [64] * 47 + [65]),           # T = 3073
     (4, 1, [1, 200, 1, 3, 820]),        # T = 1025, ranges that cross several sequences
     # Fewer tiles than waves, so as many pieces as tiles to merge, four waves in turn: up to 1,
     # 3 and 4, 5, 7 and 8, 9, 12, 13 and 16 pieces a wave.
