@@ -128,7 +128,9 @@ __device__ __forceinline__ float* f32_dst_row(const F32Dst& dst, int m, size_t l
 // partial tiles are added in wave order.  At 128 tokens x width 256, against the four waves
 // sharing the tile and walking all of K together: 12.8 -> 6.4 us a product (the backward's
 // products, one wave per 64 elements: 30.7 -> 4.6 to 6.6 us).
-template <bool AK, bool BK_>
+// KN: values of k a wave multiplies per step, 32, or 16 for K <= 64, so that all four waves
+// have some (a bound taken from K in place of a constant made every product 2 to 4 % longer).
+template <bool AK, bool BK_, int KN>
 __global__ __launch_bounds__(256) void gemm_f32_split_kernel(const float* __restrict__ A, size_t lda, WRows B,
                                                              size_t ldb, int M, int N, int K, F32Dst dst, size_t ldc,
                                                              const float* res) {
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(256) void gemm_f32_split_kernel(const float* __rest
     __shared__ float sh[4][2][32 * LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tx = lane & 7, ty = lane >> 3;
     const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
-    const int kw = (K + 4 * KS - 1) / (4 * KS) * KS, kb = wave * kw, ke = min(kb + kw, K);
+    const int kw = (K + 4 * KN - 1) / (4 * KN) * KN, kb = wave * kw, ke = min(kb + kw, K);
     float* as = sh[wave][0];
     float* bs = sh[wave][1];
     f32x4 av[4], bv[4];
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(256) void gemm_f32_split_kernel(const float* __rest
         wave_sync();
         // Rows ty + 8 i (k-contiguous) or 4 ty + i of the tile; columns likewise.
 #pragma unroll 2
-        for (int kk = 0; kk < KS; kk += 4) {
+        for (int kk = 0; kk < KN; kk += 4) {
             f32x4 a[4], b[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -286,8 +288,11 @@ hipError_t launch_f32(const float* a, size_t lda, const WRows& b, size_t ldb, in
     if ((int64_t)((M + 63) / 64) * ((N + 63) / 64) >= 256)
         hipLaunchKernelGGL((gemm_f32_kernel<AK, BK_>), dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, a, lda, b,
                            ldb, M, N, K, dst, ldc, res);
+    else if (K > 64)
+        hipLaunchKernelGGL((gemm_f32_split_kernel<AK, BK_, 32>), dim3((N + 31) / 32, (M + 31) / 32), dim3(256), 0, st, a,
+                           lda, b, ldb, M, N, K, dst, ldc, res);
     else
-        hipLaunchKernelGGL((gemm_f32_split_kernel<AK, BK_>), dim3((N + 31) / 32, (M + 31) / 32), dim3(256), 0, st, a,
+        hipLaunchKernelGGL((gemm_f32_split_kernel<AK, BK_, 16>), dim3((N + 31) / 32, (M + 31) / 32), dim3(256), 0, st, a,
                            lda, b, ldb, M, N, K, dst, ldc, res);
     return hipGetLastError();
 }

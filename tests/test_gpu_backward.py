@@ -294,6 +294,10 @@ def test_backward_ignores_unwritten_slot_contents():
     (32, 2, 1, 16, [0, 1], 3, 79),           # five tiles of queries: one wave takes a second tile
     (1024, 8, 4, 128, [0, 0], 4, 260),       # products that fill the chip (64 x 64 tiles)
     (48, 3, 1, 16, [0, 0], 2, 33),           # a width that is no multiple of 32
+    # Products of at most 64 terms, and of a few more.
+    (64, 4, 2, 16, [0, 0], 2, 16),
+    (64, 4, 2, 16, [0, 0], 4, 17),
+    (80, 5, 1, 16, [0, 0], 1, 5),
 ])
 def test_backward_fp32_over_the_tile_sizes(h, a, g, d, tau, B, S):
     w = small_workload(f"bwd32t-h{h}-a{a}-g{g}-d{d}", len(tau), h, a, g, tau, dtype="fp32", d_h=d, seed=29)
