@@ -11,7 +11,8 @@
 // rows read from global memory: dK/dV 1150 -> 19 us, dQ and the row statistics 719 -> 21 us;
 // the forward 22 -> 14 us against one wave per (token, head).  Unrolling the row loops or
 // masking by selects instead of branches made all three slower (14 -> 17, 21 -> 26, 19 -> 27
-// us): a kernel this short also pays for the instructions it fetches.
+// us): a kernel this short also pays for the instructions it fetches.  Short sequences take
+// the forward by rows (attn_seq_f32).
 //
 // A key or query outside the causal mask is never multiplied into a sum, so a value that is
 // not finite reaches only the rows that see it.
@@ -354,6 +355,14 @@ __global__ __launch_bounds__(256) void dkv_f32_kernel(AttnBwdF32 A) {
 
 hipError_t attn_seq_f32(const float* q, const float* kc, const float* vc, float* o, int B, int S, int a, int g, int d,
                         int cap, hipStream_t st) {
+    // Short sequences: one wave per (token, head), as in decode, where the device has a SIMD for
+    // each and the longest has few keys.  Prefill of four (8 heads, 8 and more sequences: two)
+    // layers on tiles over that by rows: one head of 128, 4 x 5 tokens 96 us / 72 us = 1.34, 4 x
+    // 32 1.17, 4 x 48 1.02; 8 heads of 128, 8 x 16 (1024 waves) 1.17, 16 x 16 0.98, 8 x 24 1.00,
+    // 4 x 48 0.86; 4 heads of 64, 8 x 32 1.07, 16 x 24 0.97; 4 heads of 16, 1 x 16 1.02, 1 x 24
+    // 0.98; 8 heads of 32, 8 x 16 1.05, 8 x 24 0.97.
+    if (S <= (d >= 64 ? 32 : 16) && (int64_t)B * S * a <= 1024)
+        return attn_rows_f32(q, kc, vc, o, B, S, a, g, d, cap, st);
     const dim3 grid((S + FT - 1) / FT * B * a), block(256);
     switch (d) {
         case 16: hipLaunchKernelGGL(attn_tile_f32_kernel<16>, grid, block, 0, st, q, kc, vc, o, B, S, a, g, cap); break;

@@ -209,6 +209,9 @@ hipError_t attn_f32(const float* q, const float* kc, const float* vc, const int3
 // The same over whole sequences: q [B*S][a*d], causal.
 hipError_t attn_seq_f32(const float* q, const float* kc, const float* vc, float* o, int B, int S, int a, int g, int d,
                         int cap, hipStream_t st);
+// The same, one wave per (token, head) (attn_seq_f32 takes it for few tokens).
+hipError_t attn_rows_f32(const float* q, const float* kc, const float* vc, float* o, int B, int S, int a, int g, int d,
+                         int cap, hipStream_t st);
 
 // ---- fp32 backward (vector ALU) ---------------------------------------------
 

@@ -302,17 +302,11 @@ hipError_t launch_f32(const float* a, size_t lda, const WRows& b, size_t ldb, in
 // wave reductions (online softmax in fp32), and lane j accumulates output dimensions j and
 // j + 64 over the chunk's keys, each key's weight broadcast from its lane.
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q,
-                                                       const float* __restrict__ kc,
-                                                       const float* __restrict__ vc,
-                                                       const int32_t* __restrict__ lens,
-                                                       float* __restrict__ o, int rows, int a, int g,
-                                                       int cap) {
+__device__ __forceinline__ void attn_row_f32(const float* __restrict__ q, const float* __restrict__ kc,
+                                             const float* __restrict__ vc, float* __restrict__ o, int r, int h, int b,
+                                             int pos, int a, int g, int cap, int lane) {
     constexpr int DPL = (D + 63) / 64;   // output dimensions per lane
-    const int wid = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63;
-    if (wid >= rows * a) return;         // wave-uniform
-    const int r = wid / a, h = wid - r * a, kvh = h / (a / g);
-    const int b = r, pos = max(0, min(lens[r], cap - 1));
+    const int kvh = h / (a / g);
     const float scale = 1.0f / sqrtf((float)D);
     float qv[D];
 #pragma unroll
@@ -355,6 +349,31 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
         const int d = lane + 64 * k;
         if (d < D) o[((size_t)r * a + h) * D + d] = acc[k] * inv;
     }
+}
+
+// Row r: sequence r at position lens[r].
+template <int D>
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q,
+                                                       const float* __restrict__ kc,
+                                                       const float* __restrict__ vc,
+                                                       const int32_t* __restrict__ lens,
+                                                       float* __restrict__ o, int rows, int a, int g,
+                                                       int cap) {
+    const int wid = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63;
+    if (wid >= rows * a) return;         // wave-uniform
+    const int r = wid / a, h = wid - r * a;
+    attn_row_f32<D>(q, kc, vc, o, r, h, r, max(0, min(lens[r], cap - 1)), a, g, cap, lane);
+}
+
+// Row r: sequence r / S at position r % S.
+template <int D>
+__global__ __launch_bounds__(256) void attn_rows_f32_kernel(const float* __restrict__ q, const float* __restrict__ kc,
+                                                            const float* __restrict__ vc, float* __restrict__ o,
+                                                            int rows, int S, int a, int g, int cap) {
+    const int wid = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63;
+    if (wid >= rows * a) return;         // wave-uniform
+    const int r = wid / a, h = wid - r * a, b = r / S;
+    attn_row_f32<D>(q, kc, vc, o, r, h, b, r - b * S, a, g, cap, lane);
 }
 
 }  // namespace
@@ -407,6 +426,20 @@ hipError_t attn_f32(const float* q, const float* kc, const float* vc, const int3
         case 32: hipLaunchKernelGGL(attn_f32_kernel<32>, grid, block, 0, st, q, kc, vc, lens, o, rows, a, g, cap); break;
         case 64: hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, st, q, kc, vc, lens, o, rows, a, g, cap); break;
         case 128: hipLaunchKernelGGL(attn_f32_kernel<128>, grid, block, 0, st, q, kc, vc, lens, o, rows, a, g, cap); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t attn_rows_f32(const float* q, const float* kc, const float* vc, float* o, int B, int S, int a, int g, int d,
+                         int cap, hipStream_t st) {
+    const int rows = B * S;
+    const dim3 grid((rows * a + 3) / 4), block(256);
+    switch (d) {
+        case 16: hipLaunchKernelGGL(attn_rows_f32_kernel<16>, grid, block, 0, st, q, kc, vc, o, rows, S, a, g, cap); break;
+        case 32: hipLaunchKernelGGL(attn_rows_f32_kernel<32>, grid, block, 0, st, q, kc, vc, o, rows, S, a, g, cap); break;
+        case 64: hipLaunchKernelGGL(attn_rows_f32_kernel<64>, grid, block, 0, st, q, kc, vc, o, rows, S, a, g, cap); break;
+        case 128: hipLaunchKernelGGL(attn_rows_f32_kernel<128>, grid, block, 0, st, q, kc, vc, o, rows, S, a, g, cap); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

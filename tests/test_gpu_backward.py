@@ -298,6 +298,11 @@ def test_backward_ignores_unwritten_slot_contents():
     (64, 4, 2, 16, [0, 0], 2, 16),
     (64, 4, 2, 16, [0, 0], 4, 17),
     (80, 5, 1, 16, [0, 0], 1, 5),
+    # The forward's attention by rows, and with one token or one sequence more by tiles.
+    (64, 1, 1, 64, [0, 0], 1, 32),
+    (64, 1, 1, 64, [0, 0], 2, 33),
+    (1024, 8, 4, 128, [0], 8, 16),           # 1024 rows of all heads
+    (1024, 8, 4, 128, [0], 9, 16),
 ])
 def test_backward_fp32_over_the_tile_sizes(h, a, g, d, tau, B, S):
     w = small_workload(f"bwd32t-h{h}-a{a}-g{g}-d{d}", len(tau), h, a, g, tau, dtype="fp32", d_h=d, seed=29)
