@@ -3,8 +3,8 @@
 //   rope_scatter  -- RoPE on fp32 projections, then Q to its buffer and K, V
 //                    (transposed) into the producer's slot; used by decode
 //                    (position len_b of each sequence) and by fp32 models.
-//   gemm_f32, attn_f32 -- the full-precision path for fp32 models (vector
-//                    ALU, no reduced-precision matrix modes).
+//   gemm_f32 (_nn, _tn), attn_f32, attn_rows_f32 -- the full-precision path for fp32 models
+//                    (vector ALU, no reduced-precision matrix modes).
 #include <math.h>
 
 #include "attn_f32.h"
