@@ -286,10 +286,17 @@ __device__ __forceinline__ const uint16_t* w_row3(const WRows& w, int n, int K) 
 //      it more (6144 columns, 8 rows: +0.5 us).
 //   1  by the waves themselves ahead of the barrier.
 //   0  behind it, by the threads that use them: the compiler keeps more of the weight loads in
-//      flight, which matters to workgroups of many waves (one or two to a CU).  Two layers'
-//      average, us, 1 / 0: K 8192, 64/16 heads, 12 rows 48.1 / 44.9; K 7168, 16 rows 44.2 /
-//      41.8; K 6144, 8 rows 27.7 / 26.5; K 5120, 8 rows 20.1 / 20.9, 16 rows 26.2 / 25.1;
-//      K 4096, 4 rows 13.3 / 14.0.
+//      flight, which counts where the weights come from HBM (a stack larger than the last-level
+//      cache, or long contexts).
+// 0 is better but for few rows (4, at 10 waves 2) at 8 to 10 waves and at most two workgroups
+// per CU, and for 9 to 14 rows at up to 7 waves and more than that.  Decode steps of stacks of 200 MB
+// and more, us, 1 / 0: K 2048, 16/16 heads, 20 layers, 1 row 456 / 452, 8 rows 509 / 497; K
+// 4096, 32/8, 8 layers, 2 rows 254 / 256, 4 rows 262.5 / 262.1; 32/32, 6 layers, 2 rows 249 /
+// 244, 8 rows 275 / 264; K 4608, 36/4, 6 layers, 4 rows 250 / 253, 16 rows 325 / 321; K 5120,
+// 40/8, 6 layers, 4 rows 284 / 281, 16 rows 374 / 367, 2 layers, 2 rows 79.0 / 79.8; K 6144,
+// 48/8, 5 layers, 4 rows 262 / 259; K 8192, 64/8, 4 layers, 16 rows 412 / 401; K 3072, 24/24 (576
+// workgroups), 10 layers, 8 rows 360 / 352, 9 rows 384 / 403, 14 rows 429 / 440; K 3584, 28/28,
+// 7 layers, 16 rows 342 / 336.
 // Between the waves' own loads and products they spilled the loads (14 -> 36 us).
 template <int MODE, int CS>   // MODE 0: projections with RoPE + cache append, 1: output projection + residual
 __global__ __launch_bounds__(1024) void gemm_decode_fused_kernel(const uint16_t* __restrict__ X, WRows W, int M,
@@ -298,12 +305,12 @@ __global__ __launch_bounds__(1024) void gemm_decode_fused_kernel(const uint16_t*
     __shared__ float red[16][16 * 16];   // [wave][row * 16 + column]
     __shared__ float2 cs_s[CS ? 16 * 8 : 1];   // [row][rotary pair of the workgroup]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6,
-              nw = CS == 2 ? K / 512 : blockDim.x >> 6;
+              nw = CS ? K / 512 : blockDim.x >> 6;
     const int col = lane & 15, kg = lane >> 4;
     const int j = blockIdx.x;
     const int nrot = MODE == 0 ? (fq.a + (fq.producer ? fq.g : 0)) * D : 0;   // rotary columns
     const bool rot = 16 * j < nrot;
-    if (CS != 2 || wave < nw) {
+    if (CS == 0 || wave < nw) {   // CS 1: always so, but its loads are better spread with the test
         const int n = rot ? (j >> 3) * D + (col < 8 ? 0 : HALF) + (j & 7) * 8 + (col & 7) : 16 * j + col;
         const int k0 = 512 * wave;
         const uint16_t* wr = w_row3(W, n, K) + k0 + 8 * kg;
@@ -426,7 +433,7 @@ hipError_t gemm_decode_qkv_fused_bf16(const uint16_t* x, const WRows& w, int B, 
     if (extra)
         hipLaunchKernelGGL((gemm_decode_fused_kernel<0, 2>), dim3(N / 16), dim3(64 * (waves + 1)), 0, st, x, w, B, N, K, fq,
                            FusedResid{});
-    else if (waves <= 8 || (waves <= 11 && B <= 8))
+    else if (N / 16 <= 512 ? waves >= 8 && waves <= 10 && B <= (waves < 10 ? 4 : 2) : waves <= 7 && B > 8 && B <= 14)
         hipLaunchKernelGGL((gemm_decode_fused_kernel<0, 1>), dim3(N / 16), dim3(64 * waves), 0, st, x, w, B, N, K, fq,
                            FusedResid{});
     else

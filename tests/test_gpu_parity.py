@@ -205,6 +205,42 @@ def test_decode_fused_projections_equal_split_k():
         assert torch.equal(out[16][1][p][1], out[17][1][p][1])
 
 
+@pytest.mark.parametrize("h,a,g,rows", [
+    (4096, 32, 8, (1, 4, 5, 16)),     # 8 waves: ahead of the barrier up to 4 rows
+    (5120, 40, 8, (2, 3)),            # 10 waves: up to 2
+    (3072, 24, 24, (8, 9, 14, 15)),   # 6 waves, 576 workgroups: 9 to 14 rows
+    (1536, 12, 4, (1, 16)),           # at most one workgroup per CU: by a wave of their own
+])
+def test_decode_projection_forms_append_the_same_bits(h, a, g, rows):
+    """Where the fused projections compute a position's cosines and sines is chosen by the
+    sizes; whichever form a batch takes, a producer appends the bits that the split-K path
+    (17 sequences) appends."""
+    w = small_workload(f"dec-forms-h{h}-g{g}", 1, h, a, g, [0])
+    lens17 = [(23 * i + 5) % 190 for i in range(17)]
+    say(f"[projection forms] h={h} g={g} rows={rows}")
+    dm = build_device_model(w, 17, 1, 192, fill_cache_npos=192)
+    x = torch.empty((17, w.h), dtype=tdtype(w), device=DEV)
+    kd.fill_decode_x(w, x.data_ptr(), 17)
+    y = torch.empty_like(x)
+    lens_t = torch.tensor(lens17, dtype=torch.int32, device=DEV)
+    K, V = dm.slots[0]
+    first = None
+    for B in (17, *rows):
+        for b in range(17):
+            K[b, :, lens17[b]] = 0
+            V[b, :, :, lens17[b]] = 0
+        ws_t, n = workspace(dm, kb.KVP_PHASE_DECODE, B)
+        dm.model.kvp_decode_step(x.data_ptr(), lens_t.data_ptr(), max(lens17), y.data_ptr(), B,
+                                 ws_t.data_ptr(), n, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got = [(K[b, :, lens17[b]].clone(), V[b, :, :, lens17[b]].clone()) for b in range(B)]
+        if first is None:
+            first = got
+            assert all(bool(k.any()) and bool(v.any()) for k, v in first)
+        for b in range(B):
+            assert torch.equal(got[b][0], first[b][0]) and torch.equal(got[b][1], first[b][1]), (B, b)
+
+
 def test_identity_map_equals_unshared_run_of_same_weights():
     """A shared map and the identity map differ only in which K/V a layer reads."""
     w = small_workload("map-vs-identity", 2, 512, 4, 2, [0, 0])
