@@ -9,7 +9,7 @@
 // T mod W of the waves), whatever the mix of lengths, and a range may run
 // from the end of one pair into the next without a pipeline bubble.  (With ranges of
 // ceil(T / W) tiles the last waves had none: 8 sequences of 4100 positions are 4.004
-// tiles a wave, 5 for four fifths of the waves, 26.7 us.)  Lists of up to 3 tiles a wave
+// tiles a wave, 5 for four fifths of the waves, 26.7 us.)  Some short lists
 // run on fewer waves (Split).  Each piece
 // of a range that lies in one pair ends in a partial result (running max m, sum
 // l, unnormalised O); the piece of wave w in pair P goes to slot w + P, which is
@@ -65,16 +65,21 @@ __device__ __forceinline__ SeqTiles seq_tiles(const int32_t* lens, int B, int ca
 // (T < 2^31: 64 sequences of at most 2^17 tiles and at most 256 KV heads).  Waves with one
 // tile more than others are spread over the grid: starts at one power-of-two stride (64
 // sequences of 32K: 256 tiles) meet in the same memory channels, 0.7 % slower.
-// Up to 3 tiles a wave, no more waves run than it takes at ceil(T / waves) tiles each: the
-// longest range is the same, and up to 768 waves of a short range finish sooner than 1024
-// (32/8 heads, T / waves, us, all waves / as few as it takes: 1.06 15.1 / 13.2, 1.5 15.6 /
-// 13.9, 1.75 15.9 / 15.6, 2.06 20.1 / 16.6, 2.25 19.8 / 17.7, 2.75 20.3 / 20.1).  Beyond, all
-// waves: 3.06 23.7 / 24.1, 4.06 27.9 / 28.2, 6.06 35.9 / 36.9 (5.4, the other way, 34.3 / 33.3).
+// Where it takes at most 3/4 of the waves to give none more than ceil(T / waves) = 2 or 3 tiles,
+// no more run: the longest range is the same, and 768 waves of a short range finish sooner than
+// 1024.  Decode steps, us, all waves / as few as it takes, 8/4 heads, 24 layers: T / waves 1.25
+// 979 / 937, 1.5 980 / 943, 1.75 (896 waves) 995 / 1005, 2.25 1086 / 1044, 2.5 1094 / 1115, 2.75
+// 1104 / 1134, on pages 1117 / 1164; 32/8, 6 layers: 1.5 288 / 279, 1.75 291 / 295, 2.25 315 / 305,
+// 2.5 317 / 324.  The attention alone at 3.06 (784 waves) 23.7 / 24.1, 4.06 27.9 / 28.2, 6.06
+// 35.9 / 36.9.
 struct Split {
     uint32_t T, W, q, rem;
     static __device__ __forceinline__ uint32_t waves_of(uint32_t T, uint32_t waves) {
         // Constant divisors: a division by a value of the list's took each kernel 0.1 us.
-        return T <= waves ? T : T <= 2 * waves ? (T + 1) / 2 : T <= 3 * waves ? (T + 2) / 3 : waves;
+        if (T <= waves) return T;
+        if (T <= waves + waves / 2) return (T + 1) / 2;
+        if (T > 2 * waves && T <= 2 * waves + waves / 4) return (T + 2) / 3;
+        return waves;
     }
     __device__ __forceinline__ Split(uint32_t T_, uint32_t waves) : T(T_), W(waves_of(T_, waves)), q(T_ / W), rem(T_ % W) {}
     __device__ __forceinline__ uint32_t start(uint32_t w) const { return w * q + w * rem / W; }   // w <= W <= 4096

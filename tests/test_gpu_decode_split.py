@@ -1,7 +1,7 @@
-"""The decode attention deals its list of 64-position tiles over 1024 waves (256 CUs), or over
-as few waves as it takes at one, two or three tiles each.  One tile fewer, as many, one more than
-waves, and the same around twice and three times as many, with one and with two KV heads; and a
-single tile; against the fp64 oracle at the bf16 tolerance."""
+"""The decode attention deals its list of 64-position tiles over 1024 waves (256 CUs), or, where
+768 waves or fewer are enough for one, two or three tiles each, over as few as it takes.  Tile
+counts around those limits, with one, two and three KV heads; and a single tile; against the fp64
+oracle at the bf16 tolerance."""
 import pytest
 import torch
 
@@ -25,8 +25,12 @@ def _gpu():
     (4, 1, [64] * 15 + [63]),           # T = 1023
     (4, 1, [64] * 16),                  # T = 1024
     (4, 1, [64] * 15 + [65]),           # T = 1025
+    (4, 1, [64] * 24),                  # T = 1536: the last on half as many waves as tiles
+    (4, 1, [64] * 23 + [65]),           # T = 1537
     (4, 2, [64] * 16),                  # T = 2048
     (4, 2, [64] * 15 + [65]),           # T = 2050
+    (4, 2, [64] * 18),                  # T = 2304: the last on a third
+    (4, 2, [64] * 17 + [65]),           # T = 2306
     (4, 2, [64] * 23 + [63]),           # T = 3070
     (6, 3, [64] * 16),                  # T = 3072
     (4, 1, [64] * 47 + [65]),           # T = 3073
