@@ -312,6 +312,9 @@ __global__ __launch_bounds__(64, 1) void decode_attn_kernel(
 // piece after the other took (step of two layers, 16/1 heads, one sequence of 120 000: 1024
 // pieces) 204 us, this 81; 64/8 heads, 8000: 162 and 152; batches of 4 alone 97 and 152, of 16
 // 72 and 155 (their remainder goes one by one).
+// MANY: with the batches.  Without them, for up to 8 tiles a sequence (at most two pieces a wave),
+// the kernel is half as long and takes 26 registers for 50.  Same bits.
+template <bool MANY>
 __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
     const float* __restrict__ part, const int32_t* __restrict__ lens, uint16_t* __restrict__ O, int B,
     int a, int g, int cap, int W) {
@@ -355,8 +358,10 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(
             }
         };
         int s = 0;
-        for (; s + 8 <= c; s += 8) add(std::integral_constant<int, 8>{}, s);
-        for (; s + 4 <= c; s += 4) add(std::integral_constant<int, 4>{}, s);
+        if constexpr (MANY) {
+            for (; s + 8 <= c; s += 8) add(std::integral_constant<int, 8>{}, s);
+            for (; s + 4 <= c; s += 4) add(std::integral_constant<int, 4>{}, s);
+        }
         for (; s < c; ++s) add(std::integral_constant<int, 1>{}, s);
     }
     *(f32x2*)&num_s[wave][2 * lane] = num;
@@ -398,10 +403,14 @@ hipError_t decode_attn_bf16(const uint16_t* q, const uint16_t* kc, const uint16_
 }
 
 hipError_t decode_combine_bf16(const float* part, const int32_t* lens, uint16_t* o, int B, int a, int g,
-                               int cap, int waves, hipStream_t st) {
+                               int cap, int waves, int max_len, hipStream_t st) {
     if (B < 1 || B > 64 || waves < 1 || waves > kMaxDecodeSplits) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(decode_combine_kernel, dim3(B * a), dim3(kCombineThreads), 0, st, part, lens, o, B,
-                       a, g, cap, waves);
+    if (max_len >= 8 * TILE)
+        hipLaunchKernelGGL(decode_combine_kernel<true>, dim3(B * a), dim3(kCombineThreads), 0, st, part, lens, o, B, a,
+                           g, cap, waves);
+    else
+        hipLaunchKernelGGL(decode_combine_kernel<false>, dim3(B * a), dim3(kCombineThreads), 0, st, part, lens, o, B, a,
+                           g, cap, waves);
     return hipGetLastError();
 }
 

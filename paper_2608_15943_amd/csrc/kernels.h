@@ -181,7 +181,7 @@ hipError_t decode_attn_bf16(const uint16_t* q, const uint16_t* kc, const uint16_
                             const int32_t* lens, float* part, int B, int a, int g, int cap, int waves,
                             const Pages& pages, hipStream_t st);
 hipError_t decode_combine_bf16(const float* part, const int32_t* lens, uint16_t* o, int B, int a, int g,
-                               int cap, int waves, hipStream_t st);
+                               int cap, int waves, int max_len, hipStream_t st);   // len_b <= max_len
 
 // ---- shared by both dtypes -------------------------------------------------
 

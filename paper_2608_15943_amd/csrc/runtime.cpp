@@ -406,7 +406,7 @@ int run_decode_layer(kvp_ctx* c, int l, const LayerIO& io, const int32_t* lens,
             return rc;
         if ((rc = timed(c, KVP_K_DEC_COMBINE, st, [&] {
                  return check_hip(kvp::decode_combine_bf16(part, lens, (uint16_t*)o, B, c->d.a, c->d.g,
-                                                           kv.cap, c->decode_waves, st),
+                                                           kv.cap, c->decode_waves, max_len, st),
                                   "decode combine");
              })))
             return rc;
