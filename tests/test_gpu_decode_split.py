@@ -1,7 +1,7 @@
-"""The decode attention deals its list of 64-position tiles over 1024 waves (256 CUs), or, where
-768 waves or fewer are enough for one, two or three tiles each, over as few as it takes.  Tile
-counts around those limits, with one, two and three KV heads; and a single tile; against the fp64
-oracle at the bf16 tolerance."""
+"""The decode attention deals its list of 64-position tiles over 1024 waves (256 CUs), over one
+wave per tile when there are fewer, or, where 768 waves or fewer are enough for two or three
+tiles each, over as few as it takes.  Tile counts around those limits, with one, two and three KV
+heads; and a single tile; against the fp64 oracle at the bf16 tolerance."""
 import pytest
 import torch
 
